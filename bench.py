@@ -744,7 +744,7 @@ def main() -> int:
     sched_name = {B.VERIFY_ONE_SWEEP: "one-sweep", B.VERIFY_TWO_SWEEP: "two-sweep",
                   B.VERIFY_ONE_SWEEP_PERSISTENT: "one-sweep persistent"}[schedule]
     verify_kernels = {B.VERIFY_ONE_SWEEP: "verify_fused_kernel",
-                      B.VERIFY_ONE_SWEEP_PERSISTENT: "verify_pipe_kernel",
+                      B.VERIFY_ONE_SWEEP_PERSISTENT: "verify_stream_kernel",
                       B.VERIFY_TWO_SWEEP: "verify_stats_kernel + verify_main_kernel + verify_combine_kernel"}[schedule]
 
     stream = torch.cuda.current_stream()

@@ -138,7 +138,7 @@ typedef struct {
 /* How ssl_verify_attn schedules its work (results agree to rounding):
  *  AUTO       a one-sweep schedule where one fits and a KV head has at most
  *             32 verify rows, or more when its chunks run in one round of
- *             workgroups, or up to 48 when the persistent form runs (their
+ *             workgroups, or up to 48 when the streaming form runs (their
  *             measured sweet spots), else the two-sweep one;
  *  TWO_SWEEP  a K-only pass for the row statistics, then a K+V pass;
  *  ONE_SWEEP  a single K+V pass whose chunks of one (sequence, KV head)
@@ -147,12 +147,14 @@ typedef struct {
  *             round of workgroups (a (sequence, KV head) may then span at most
  *             128 chunks of at most 2048 / 1024 / 640 / 512 keys for up to
  *             16 / 32 / 48 / 64 verify rows per KV head), else, for up to 48
- *             rows, a persistent grid of what the device holds at once (see
- *             ssl_set_cu_budget), each workgroup taking every grid-th chunk
- *             and keeping two chunks' probabilities in 16-bit form (relative
- *             error 2^-11; probabilities below 2^-54 of the row's running
- *             maximum count as 0); SSL_ERR_UNSUPPORTED when neither fits.
- * ssl_verify_plan reports the persistent form as
+ *             rows, by a streaming kernel that runs two workgroups per CU over
+ *             any number of rounds and keeps its probabilities in 16-bit form
+ *             (relative error 2^-11; probabilities below 2^-54 of the row's
+ *             running maximum count as 0) when a (sequence, KV head) takes at
+ *             most 64 chunks of at most 2048 / 1024 / 640 keys, else in fp32
+ *             (at most 40 rows and 128 chunks); SSL_ERR_UNSUPPORTED when none
+ *             fits.
+ * ssl_verify_plan reports the streaming form as
  * SSL_VERIFY_ONE_SWEEP_PERSISTENT (an output only, not a request). */
 enum {
     SSL_VERIFY_AUTO = 0,
@@ -264,9 +266,10 @@ int ssl_verify_attn_static(const ssl_shape *shape, const ssl_params *params,
 
 /* The schedule ssl_verify_attn would use for these arguments: *schedule_out
  * = SSL_VERIFY_ONE_SWEEP, SSL_VERIFY_ONE_SWEEP_PERSISTENT or
- * SSL_VERIFY_TWO_SWEEP, *chunk_out = keys per work item, *items_out = work
- * items (each one workgroup, or, persistent, one chunk of a workgroup's
- * sequence).  Host only. */
+ * SSL_VERIFY_TWO_SWEEP, *chunk_out = keys per work item (the longest, where
+ * sequences have their own), *items_out = work items (each one workgroup).
+ * Host only; without a GPU the fp32 streaming form is not planned (it needs
+ * the device's occupancy). */
 int ssl_verify_plan(const ssl_shape *shape, const ssl_params *params,
                     const int32_t *ctx_len_host, const int32_t *q_len_host,
                     int32_t *schedule_out, int32_t *chunk_out, int32_t *items_out);

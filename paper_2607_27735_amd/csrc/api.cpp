@@ -171,15 +171,78 @@ struct VerifyPlan {
     bool fused_ok;
     int fused_chunk, fused_slots;
     bool one_round;  // the one-workgroup-per-chunk one sweep runs in one round of workgroups
-    bool pipe;       // one sweep by the persistent kernel: fused_slots chunks over pipe_grid workgroups
-    int pipe_grid;
-    size_t ml_off, o_off, bytes;
+    bool pipe;       // one sweep by the streaming kernel over 16-bit codes, fused_chunk keys per chunk
+    bool stream;     // one sweep by the streaming kernel: chunk_s[b] keys per chunk, stream_slots chunks
+    int stream_slots;
+    int32_t chunk_s[kTableBatch];
+    size_t ml_off, lse_off, otag_off, o_off, bytes;
     SeqTable seq;
     SeqTable fseq;   // the one-sweep slots as items
 };
 
+// The streaming one sweep (verify_stream.hip) with an fp32 stash: chunks of at
+// most what half a CU's LDS holds for each sequence's rows, shortened evenly
+// when the call has fewer chunks than the device's workgroup slots.  Taken
+// instead of two sweeps for at most 40 rows and 128 chunks per unit: more rows
+// make chunks short and their waits long (48 rows over 4 x 64K keys: 330 us
+// against 275 us for two sweeps), and more chunks keep too many of the slots
+// waiting for one unit (36 rows, 228 chunks per 131K-key head: 145 against
+// 140 us), while a ragged batch of 16K-64K keys with up to 40 rows takes 292
+// us against 383 us.  False, too, where the device does not hold two
+// workgroups per CU (or cannot be asked).
+bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, int block_pos, VerifyPlan* plan) {
+    constexpr int kTileKeys = 32, kMinTiles = 4, kSpreadTiles = 24, kMaxChunksPerUnit = 256;
+    constexpr int kStreamRows = 40, kStreamChunksPerUnit = 128;
+    plan->stream = false;
+    const int per_cu = stream_blocks_per_cu();
+    if (per_cu < 2) return false;
+    const int g = s->n_q_heads / s->n_kv_heads;
+    const int64_t slots_now = (int64_t)device_cus() * per_cu;
+    const int64_t max_per_unit = std::min<int64_t>(kMaxChunksPerUnit, resident_group_cap(per_cu));
+    int cap[kTableBatch], cap_max = 0;
+    for (int b = 0; b < s->batch; ++b) {
+        if (std::min(ql[b], block_pos) * g > kStreamRows) return false;
+        cap[b] = stream_max_tiles(std::min(ql[b], block_pos) * g);
+        if (cap[b] < kMinTiles) return false;
+        cap_max = std::max(cap_max, cap[b]);
+    }
+    auto count = [&](int limit) {
+        int64_t n = 0;
+        for (int b = 0; b < s->batch; ++b) {
+            const int keys = std::min(cap[b], limit) * kTileKeys;
+            n += (int64_t)s->n_kv_heads * ((ctx[b] + keys - 1) / keys);
+        }
+        return n;
+    };
+    // One round: the shortest chunks that still fit it.  Several: chunks of
+    // about equal length (sequences with few rows could take longer ones), so
+    // that no workgroup is still streaming when the others have finished.
+    int limit = cap_max;
+    if (count(limit) <= slots_now) {
+        while (limit > kMinTiles && count(limit - 1) <= slots_now) --limit;
+    } else {
+        int max_ctx = 0;
+        for (int b = 0; b < s->batch; ++b) max_ctx = std::max(max_ctx, ctx[b]);
+        const int need = (int)(((int64_t)max_ctx + kTileKeys * max_per_unit - 1) / (kTileKeys * max_per_unit));
+        limit = std::min(limit, std::max(kSpreadTiles, need));
+    }
+    int64_t slots = 0;
+    for (int b = 0; b < s->batch; ++b) {
+        plan->chunk_s[b] = std::min(cap[b], limit) * kTileKeys;
+        const int64_t n = (ctx[b] + plan->chunk_s[b] - 1) / plan->chunk_s[b];
+        if (n > max_per_unit || n > kStreamChunksPerUnit) return false;
+        slots += n * s->n_kv_heads;
+    }
+    if (slots > (1 << 30) / kVerifyRowCap) return false;
+    plan->stream = true;
+    plan->stream_slots = (int)slots;
+    return true;
+}
+
+// bytes_limit: the most workspace the plan may ask for where a schedule with
+// less would do (the library's own scratch).
 int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql,
-                VerifyPlan* plan) {
+                VerifyPlan* plan, size_t bytes_limit = ~(size_t)0) {
     int rc = check_shape(s);
     if (rc) return rc;
     if (!p) return SSL_ERR_NULL;
@@ -279,72 +342,88 @@ int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, con
             plan->fused_slots = (int)slots;
         }
     }
-    // Persistent one sweep, where the chunks above would take more than one
-    // round of workgroups (or do not fit at all) and a KV head has at most 48
-    // rows: a grid of what the device holds at once (the whole grid must be
-    // resident), each workgroup taking every grid-th chunk of a 16-bit stash
-    // size, a unit's chunks within two consecutive rounds (at most one grid
-    // of them) and at most kPipeMaxChunksPerUnit of them (every chunk's finish
-    // loads each chunk's statistics and its rows' partials in passes of 32
-    // chunks, one round trip each: at 103 and 256 chunks per unit the call
-    // measured slower than two sweeps).  The chunk is the one that minimises
-    // rounds * (chunk + 96): a round costs about 96 keys' streaming besides
-    // its own keys.
-    constexpr int64_t kPipeMaxChunksPerUnit = 64;
+    // One sweep over 16-bit codes, where the chunks above would take more than
+    // one round of workgroups (or do not fit at all), a KV head has at most 48
+    // rows and a unit at most kCodeMaxChunksPerUnit chunks (and within half of
+    // what the device holds, at two workgroups per CU).  The chunk is the one
+    // that minimises rounds of a workgroup per CU * (chunk + 96 keys).
+    constexpr int64_t kCodeMaxChunksPerUnit = 64;
     plan->pipe = false;
-    plan->pipe_grid = 0;
     const int64_t resident1 = n_cu * std::max(fused_blocks_per_cu(plan->row_tiles), 1);
     const bool one_round = plan->fused_ok && plan->fused_slots <= resident1;
     plan->one_round = one_round;
-    // (pipe_max_chunk is 0 where the persistent kernel is not built: > 48 rows)
+    // (stream_max_code_chunk is 0 where the kernel is not built: > 48 rows)
     if (!one_round && plan->block_pos >= s->max_q) {
-        const int64_t grid_cap = n_cu * std::max(pipe_blocks_per_cu(plan->row_tiles), 1);
-        int64_t best_cost = -1, best_chunk = 0, best_tasks = 0;
-        for (int64_t pc = pipe_max_chunk(plan->row_tiles); pc >= 128; pc -= 128) {
+        int64_t best_cost = -1, best_chunk = 0;
+        for (int64_t pc = stream_max_code_chunk(plan->row_tiles); pc >= 128; pc -= 128) {
             int64_t tasks = 0;
             for (int b = 0; b < s->batch; ++b) tasks += (int64_t)s->n_kv_heads * ((ctx[b] + pc - 1) / pc);
-            const int64_t grid = std::min(tasks, grid_cap);
+            const int64_t grid = std::min(tasks, n_cu);
             const int64_t per_unit = (max_ctx + pc - 1) / pc;
-            if (per_unit > grid || per_unit > kPipeMaxChunksPerUnit || tasks > (1 << 30)) continue;
+            if (per_unit > grid || per_unit > kCodeMaxChunksPerUnit || tasks > (1 << 30)) continue;
             const int64_t cost = (tasks + grid - 1) / grid * (pc + 96);
             if (best_cost < 0 || cost < best_cost) {
                 best_cost = cost;
                 best_chunk = pc;
-                best_tasks = tasks;
             }
         }
         if (best_cost >= 0) {
-            plan->fseq = plan->seq;
-            int64_t slots = 0;
-            for (int b = 0; b < s->batch; ++b) {
-                plan->fseq.item_start[b] = (int32_t)slots;
-                slots += (int64_t)s->n_kv_heads * ((ctx[b] + best_chunk - 1) / best_chunk);
-            }
-            plan->fseq.item_start[s->batch] = (int32_t)slots;
             plan->fused_ok = true;
-            plan->fused_chunk = (int)best_chunk;
-            plan->fused_slots = (int)best_tasks;
             plan->pipe = true;
-            plan->pipe_grid = (int)std::min(best_tasks, grid_cap);
+            plan->fused_chunk = (int)best_chunk;
+            plan->fused_slots = 0;
+            for (int b = 0; b < s->batch; ++b)
+                plan->fused_slots += s->n_kv_heads * (int)((ctx[b] + best_chunk - 1) / best_chunk);
         }
     }
     if (p->verify_mode == SSL_VERIFY_ONE_SWEEP && !plan->fused_ok) return SSL_ERR_UNSUPPORTED;
     const size_t slots_max = (size_t)std::max(plan->n_items, plan->fused_slots);
     // per item and row: (max, sum), each word tagged in the one-sweep schedule
     plan->ml_off = kEpochBytes;
+    plan->lse_off = plan->otag_off = 0;
     plan->o_off = plan->ml_off + align_up(slots_max * kVerifyRowCap * sizeof(uint64_t) * 2);
     plan->bytes = plan->o_off + align_up(slots_max * kVerifyRowCap * 128 * sizeof(float));
+    // The streaming kernel's chunks: of 16-bit codes as planned above, else of
+    // fp32 where that beats two sweeps (see plan_stream).
+    plan->stream = false;
+    if (p->verify_mode == SSL_VERIFY_TWO_SWEEP) return SSL_OK;
+    if (plan->pipe) {
+        plan->stream = true;
+        plan->stream_slots = plan->fused_slots;
+        for (int b = 0; b < s->batch; ++b) plan->chunk_s[b] = plan->fused_chunk;
+    } else if (!one_round) {
+        plan_stream(s, ctx, ql, plan->block_pos, plan);
+    }
+    if (plan->stream) {
+        int64_t rows_out = 0;
+        for (int b = 0; b < s->batch; ++b)
+            rows_out += (int64_t)s->n_kv_heads * ((ctx[b] + plan->chunk_s[b] - 1) / plan->chunk_s[b]) *
+                        std::min(ql[b], plan->block_pos) * g;
+        const size_t lse_off = plan->ml_off + align_up((size_t)plan->stream_slots * kVerifyRowCap * sizeof(uint64_t) * 2);
+        const size_t otag_off = lse_off + align_up((size_t)s->batch * s->n_kv_heads * kVerifyRowCap * sizeof(uint64_t));
+        const size_t o_off = otag_off + align_up((size_t)plan->stream_slots * sizeof(uint64_t));
+        const size_t bytes = o_off + align_up((size_t)rows_out * 128 * sizeof(float));
+        if (bytes > bytes_limit && plan->bytes <= bytes_limit && !plan->pipe) {
+            plan->stream = false;
+        } else {
+            plan->lse_off = lse_off;
+            plan->otag_off = otag_off;
+            plan->o_off = o_off;
+            plan->bytes = std::max(plan->bytes, bytes);
+        }
+    }
     return SSL_OK;
 }
 
 // AUTO takes one sweep where it fits and a KV head has at most 32 verify rows,
 // or more when it runs in one round of workgroups or (up to 48 rows) in the
-// persistent form; over several rounds at 33-64 rows (one wave per SIMD,
+// streaming form; over several rounds at 33-64 rows (one wave per SIMD,
 // logits of every row in LDS) the one-workgroup-per-chunk kernel waits
 // across rounds and two sweeps are faster (70B shape: 457 vs 336 us), while
 // in one round it wins (44 rows at 16K: 26.1 vs 36.5 us; 48 rows at 8K: 21.8
 // vs 29.6 us; 64 rows at 8K: 25.2 vs 34.0 us).
 bool use_one_sweep(const VerifyPlan& plan, const ssl_params* p) {
+    if (plan.stream) return true;
     if (!plan.fused_ok || p->verify_mode == SSL_VERIFY_TWO_SWEEP) return false;
     return p->verify_mode == SSL_VERIFY_ONE_SWEEP || plan.row_tiles <= 2 || plan.pipe || plan.one_round;
 }
@@ -551,6 +630,12 @@ int ssl_verify_plan(const ssl_shape* shape, const ssl_params* params, const int3
     const int rc = plan_verify(shape, params, ctx_len_host, q_len_host, &plan);
     if (rc) return rc;
     const bool one = use_one_sweep(plan, params);
+    if (plan.stream) {
+        *schedule_out = SSL_VERIFY_ONE_SWEEP_PERSISTENT;
+        *chunk_out = *std::max_element(plan.chunk_s, plan.chunk_s + shape->batch);
+        *items_out = plan.stream_slots;
+        return SSL_OK;
+    }
     *schedule_out = !one ? SSL_VERIFY_TWO_SWEEP : plan.pipe ? SSL_VERIFY_ONE_SWEEP_PERSISTENT : SSL_VERIFY_ONE_SWEEP;
     *chunk_out = one ? plan.fused_chunk : plan.chunk;
     *items_out = one ? plan.fused_slots : plan.n_items;
@@ -573,13 +658,48 @@ int check_paged(const ssl_shape* s, const int32_t* ctx, const int32_t* block_tab
     return SSL_OK;
 }
 
+// The tables of block k of a streaming launch (blocks of plan.block_pos verify
+// positions, the last positions of every sequence first; a block holds only
+// the sequences that still have positions).  Returns its chunks.
+int stream_block(const ssl_shape* shape, const VerifyPlan& plan, const int32_t* ctx, const int32_t* ql, int k,
+                 StreamArgs* sa) {
+    VerifyArgs& v = sa->v;
+    memset(&v.seq, 0, sizeof v.seq);
+    const int P = plan.block_pos;
+    int n = 0;
+    int64_t items = 0, rows = 0;
+    for (int b = 0; b < shape->batch; ++b) {
+        const int j_end = ql[b] - k * P;
+        if (j_end <= 0) continue;
+        const int j0 = std::max(0, j_end - P);
+        const int64_t nchunk = (ctx[b] + plan.chunk_s[b] - 1) / plan.chunk_s[b];
+        v.seq.item_start[n] = (int32_t)items;
+        v.seq.row_start[n] = (int32_t)rows;
+        v.seq.ctx[n] = ctx[b];
+        v.seq.qlen[n] = j_end - j0;
+        v.sid[n] = b;
+        v.qoff[n] = j0;
+        v.qfull[n] = ql[b];
+        sa->chunk[n] = plan.chunk_s[b];
+        items += shape->n_kv_heads * nchunk;
+        rows += shape->n_kv_heads * nchunk * (j_end - j0) * v.group;
+        ++n;
+    }
+    v.seq.n_seq = n;
+    v.seq.item_start[n] = (int32_t)items;
+    v.seq.row_start[n] = (int32_t)rows;
+    for (int i = n + 1; i <= kTableBatch; ++i) v.seq.item_start[i] = INT32_MAX;   // past every slot
+    v.score_add = k > 0 ? 1 : 0;
+    return (int)items;
+}
+
 int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx_len_host,
                 const int32_t* q_len_host, const void* q, const void* k_cache,
                 const void* v_cache, const int32_t* block_table, int32_t page_size,
                 int32_t max_blocks, void* out, float* scores, void* workspace,
                 size_t workspace_bytes, hipStream_t stream, const StaticScratch* scratch = nullptr) {
     VerifyPlan plan;
-    int rc = plan_verify(shape, params, ctx_len_host, q_len_host, &plan);
+    int rc = plan_verify(shape, params, ctx_len_host, q_len_host, &plan, scratch ? scratch->bytes : ~(size_t)0);
     if (rc) return rc;
     if (block_table || page_size || max_blocks) {
         rc = check_paged(shape, ctx_len_host, block_table, page_size, max_blocks);
@@ -632,6 +752,29 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
         const int g = a.group;
         if (g > 16 || (g & (g - 1)) != 0) return SSL_ERR_UNSUPPORTED;
     }
+    if (plan.stream) {
+        // One launch per block of positions: a launch takes its own tag, and
+        // a later block's scores are added to the earlier ones'.
+        StreamArgs sa = {};
+        sa.v = a;
+        sa.u16 = plan.pipe ? 1 : 0;
+        sa.lse = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + plan.lse_off);
+        sa.otag = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + plan.otag_off);
+        rc = epochs_if_captured(stream, workspace, (int64_t)shape->batch * shape->n_kv_heads, &sa.epoch);
+        if (rc) return rc;
+        rc = make_exchange(&sa.xc);
+        if (rc) return rc;
+        sa.heal = scratch && !sa.epoch ? static_cast<uint64_t*>(workspace) : nullptr;
+        int max_q = 0;
+        for (int b = 0; b < shape->batch; ++b) max_q = std::max(max_q, q_len_host[b]);
+        for (int k = 0; k * plan.block_pos < max_q; ++k) {
+            const int n_slots = stream_block(shape, plan, ctx_len_host, q_len_host, k, &sa);
+            sa.call_tag = next_call_tag();
+            sa.heal_value = mix64(sa.call_tag);
+            if (const int hip_st = hip_rc(launch_verify_stream(sa, n_slots, stream))) return hip_st;
+        }
+        return SSL_OK;
+    }
     if (use_one_sweep(plan, params)) {
         FusedArgs fa = {};
         fa.v = a;
@@ -647,9 +790,7 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
         // lifting the mark a captured call that gave up may have left there.
         fa.heal = scratch && !fa.epoch ? static_cast<uint64_t*>(workspace) : nullptr;
         fa.heal_value = mix64(fa.call_tag);
-        fa.n_tasks = plan.pipe ? plan.fused_slots : 0;
-        return hip_rc(launch_verify_fused(fa, plan.pipe ? plan.pipe_grid : plan.fused_slots, plan.row_tiles,
-                                          stream));
+        return hip_rc(launch_verify_fused(fa, plan.fused_slots, plan.row_tiles, stream));
     }
     if (plan.block_pos >= shape->max_q)
         return hip_rc(launch_verify(a, plan.n_items, plan.n_rows, plan.row_tiles, stream));
@@ -1038,7 +1179,7 @@ int plan_decode(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, con
     constexpr int kStepMinChunk = 512;
     const int g = s->n_q_heads / s->n_kv_heads;
     const int64_t resident = (int64_t)device_cus() * std::max(fused_blocks_per_cu(plan->v.row_tiles), 1);
-    plan->one_kernel = use_one_sweep(plan->v, p) && !plan->v.pipe && !p->per_head && g <= 16 &&
+    plan->one_kernel = use_one_sweep(plan->v, p) && !plan->v.stream && !p->per_head && g <= 16 &&
                        plan->v.fused_slots <= resident && plan->v.fused_chunk >= kStepMinChunk;
     if (!plan->one_kernel) {
         plan->parts = 0;

@@ -181,10 +181,6 @@ struct FusedArgs {
     // units to set to heal_value + unit at the end (null otherwise).
     uint64_t* heal;
     uint64_t heal_value;
-    // Persistent schedule: n_tasks chunks (work items) over a grid of at most
-    // n_tasks workgroups, all resident at once, each taking every grid-th
-    // chunk; 0: one workgroup per chunk.
-    int32_t n_tasks;
     // Whole decode step (step = 1): after its outputs and scores, each
     // workgroup runs the one-kernel select as partition s (the chunk) of its
     // unit over the scores it has just computed, and then the first draft
@@ -192,6 +188,24 @@ struct FusedArgs {
     // of a unit, sel.with_draft = 1; same call tag, epochs and status word).
     int32_t step;
     SelectArgs sel;
+};
+
+// Single-sweep verify over several rounds of workgroups, two per CU
+// (verify_stream.hip).  The items of v.seq are (unit, chunk of chunk[bt] keys)
+// slots; v.part_ml holds each unit's tagged (max, sum) words, [row][chunk] at
+// the unit's first slot * 64, and v.part_o the partial rows, each sequence's
+// from v.seq.row_start[bt] on, [KV head][chunk][row].
+struct StreamArgs {
+    VerifyArgs v;
+    uint64_t* lse;          // [units][64] tagged log-sum-exp of each row
+    uint64_t* otag;         // [slots] tags of the chunks' partial outputs
+    uint64_t* epoch;        // [units] exchange epochs (any initial value), or null
+    uint64_t call_tag;      // this call's tag: unique within the process (see exchange_tag)
+    Exchange xc;
+    uint64_t* heal;         // as in FusedArgs
+    uint64_t heal_value;
+    int32_t u16;                  // 1: the probabilities are kept as 16-bit codes; 0: fp32
+    int32_t chunk[kTableBatch];   // keys per chunk of each sequence, a multiple of 32
 };
 
 // The library's static device scratch (the no-allocation entry point): its
@@ -206,8 +220,7 @@ struct StaticScratch {
 hipError_t launch_verify(const VerifyArgs& a, int n_items, int n_rows_total, int row_tiles,
                          hipStream_t stream);
 // Launches the single-sweep kernel over n_slots workgroups (it adds the
-// chunks of each row itself; with a.step it also selects and drafts), or,
-// with a.n_tasks > 0, the persistent one over a grid of n_slots workgroups.
+// chunks of each row itself; with a.step it also selects and drafts).
 // Returns the launch error.
 hipError_t launch_verify_fused(const FusedArgs& a, int n_slots, int row_tiles, hipStream_t stream);
 // The combine kernel alone: out[row] = sum of the row's normalised partials.
@@ -219,11 +232,14 @@ int fused_max_chunk(int row_tiles);
 // current device holds at once; 0 if the device cannot be queried.
 int fused_blocks_per_cu(int row_tiles);
 int select_blocks_per_cu(int part);
-// The persistent single-sweep kernel (FusedArgs.n_tasks > 0): the largest key
-// chunk its two 16-bit stash buffers hold (0 for row_tiles it is not built
-// for), and its workgroups per CU.
-int pipe_max_chunk(int row_tiles);
-int pipe_blocks_per_cu(int row_tiles);
+// The streaming single-sweep kernel: its workgroups per CU at the largest LDS
+// use (0 if the device cannot be queried), the 32-key tiles of the largest
+// fp32 chunk for `rows` verify rows per KV head (0 for more rows than it is
+// built for), and the keys of the largest chunk of 16-bit codes.
+int stream_blocks_per_cu();
+int stream_max_tiles(int rows);
+int stream_max_code_chunk(int row_tiles);
+hipError_t launch_verify_stream(const StreamArgs& a, int n_slots, hipStream_t stream);
 // Partition length for the longest context max_t: the smallest multiple of
 // 1024 (in powers of two, at most kSelectMaxRounds * 1024) that keeps a unit at
 // <= kSelectTargetParts partitions.

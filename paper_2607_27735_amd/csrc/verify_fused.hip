@@ -29,16 +29,13 @@
 // a clock-seeded start (consecutive calls differ in the low 32 bits for 2^32
 // calls), so a stale or uninitialised word matches only by a 2^-32 accident.
 //
-// Two kernels run these steps.  verify_fused_kernel gives each chunk its own
-// workgroup (fp32 stash; with kStep it then selects and drafts too).  Its wait
-// ends: workgroups are dispatched in index order and the chunks of one head
+// verify_fused_kernel gives each chunk its own workgroup (with kStep it then
+// selects and drafts too).  Its wait ends: workgroups are dispatched in index order and the chunks of one head
 // are consecutive, so when the lowest unfinished head waits, every workgroup
 // ahead of its chunks has finished and its chunks are resident (the host
 // plans at most half of what the device's CUs hold at once per head).
-// verify_pipe_kernel, for calls whose chunks would take several rounds of
-// workgroups, is a resident grid that takes every grid-th chunk with two
-// 16-bit stash buffers and runs steps 2-4 of one chunk while the next one
-// streams (its own comment gives the order and why its waits end).  Every
+// verify_stream.hip runs the same steps, two workgroups per CU, for calls whose
+// chunks would take several rounds of workgroups here.  Every
 // wait is also bounded: a workgroup whose wait gives up reports it on the
 // device's status word and leaves without writing scores or outputs.
 #include <algorithm>
@@ -61,41 +58,9 @@ constexpr size_t kStepRedOffset = (sizeof(SelLds) + 15) / 16 * 16;
 constexpr size_t kStepLdsMin = kStepRedOffset + 256 * sizeof(f32x4);
 static_assert(kStepLdsMin + 8 * 1024 <= 160 * 1024, "the step's LDS fits beside the static arrays");
 
-// The LDS stash holds each key's probability per verify row, relative to the
-// row's reference maximum (at most 2^kLazy).  Two element formats:
-//  - StashF32: the fp32 value (the kernel that runs one chunk per workgroup);
-//  - StashU16: a 16-bit code, half the LDS, so that the persistent kernel can
-//    keep two chunks' stashes: 6 exponent bits (2^-54 .. 2^9) above the top 10
-//    mantissa bits, rounded to nearest (relative error at most 2^-11, so a
-//    score, a sum of such terms times exact factors, keeps that bound); values
-//    below 2^-54 of the reference are coded 0.
-struct StashF32 {
-    using T = float;
-    static constexpr int kPad = 4;   // elements of padding per row
-    static __device__ __forceinline__ void put(T* p, float v) { *p = v; }
-    // keys k4 .. k4 + 3 of a row (k4 a multiple of 4)
-    static __device__ __forceinline__ f32x4 get4(const T* row, int k4) {
-        return *reinterpret_cast<const f32x4*>(row + k4);
-    }
-};
-
-struct StashU16 {
-    using T = uint16_t;
-    static constexpr int kPad = 8;
-    static constexpr uint32_t kBias = 72u << 10;   // exponent field 72 at code 0
-    static __device__ __forceinline__ uint32_t enc(float v) {
-        const uint32_t r = (__float_as_uint(v) + 0x1000u) >> 13;   // 10 mantissa bits, rounded
-        return r >= kBias + 1024u ? min(r - kBias, 0xFFFFu) : 0u;
-    }
-    static __device__ __forceinline__ float dec(uint32_t c) {
-        return c ? __uint_as_float((c + kBias) << 13) : 0.f;
-    }
-    static __device__ __forceinline__ void put(T* p, float v) { *p = (uint16_t)enc(v); }
-    static __device__ __forceinline__ f32x4 get4(const T* row, int k4) {
-        const uint2 w = *reinterpret_cast<const uint2*>(row + k4);
-        return f32x4{dec(w.x & 0xFFFFu), dec(w.x >> 16), dec(w.y & 0xFFFFu), dec(w.y >> 16)};
-    }
-};
+// The LDS stash holds each key's probability per verify row in fp32, relative
+// to the row's reference maximum (at most 2^kLazy).
+constexpr int kStashPad = 4;   // floats of padding per row
 
 template <int NRT>
 constexpr int static_lds_bytes() {
@@ -113,17 +78,17 @@ constexpr int max_fused_chunk() {
     constexpr int kLds = 160 * 1024;
     constexpr int floats_per_row =
         (kLds - static_lds_bytes<NRT>() - kParkFloats * 4 - 1024) / 4 / (16 * NRT);
-    return (floats_per_row - StashF32::kPad) * kTile / (kTile + 1) / 128 * 128;
+    return (floats_per_row - kStashPad) * kTile / (kTile + 1) / 128 * 128;
 }
 
 __device__ __forceinline__ float safe_max(float m) { return m == -INFINITY ? 0.f : m; }
 
 // One 32-key tile: online softmax and P.V; the tile's probabilities relative
 // to the rows' reference maxima go to the LDS stash, those maxima to mtile.
-template <int NRT, typename Codec>
+template <int NRT>
 __device__ __forceinline__ void fused_tile(const VerifyArgs& a, const Rows<NRT>& r,
                                            const KVTile& tl, int key0, int kl0,
-                                           typename Codec::T* stash, int stride, float* mtile,
+                                           float* stash, int stride, float* mtile,
                                            int mts, int m16, int G, float (&M)[NRT],
                                            float (&L)[NRT], f32x4 (&oacc)[8][NRT]) {
     f32x4 acc[2][NRT];
@@ -133,7 +98,7 @@ __device__ __forceinline__ void fused_tile(const VerifyArgs& a, const Rows<NRT>&
     for (int rt = 0; rt < NRT; ++rt) {
         float y[8];
         float mt = -INFINITY;
-        typename Codec::T* srow = stash + (rt * 16 + m16) * stride + kl0;
+        float* srow = stash + (rt * 16 + m16) * stride + kl0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int t = e >> 2, i = e & 3;
@@ -161,7 +126,7 @@ __device__ __forceinline__ void fused_tile(const VerifyArgs& a, const Rows<NRT>&
         for (int e = 0; e < 8; ++e) {
             p[e >> 2][rt][e & 3] = fast_exp2(y[e] - Mr);
             sum += p[e >> 2][rt][e & 3];
-            Codec::put(srow + 16 * (e >> 2) + G + 4 * (e & 3), p[e >> 2][rt][e & 3]);
+            srow[16 * (e >> 2) + G + 4 * (e & 3)] = p[e >> 2][rt][e & 3];
         }
         if (G == 0) mtile[(rt * 16 + m16) * mts + kl0 / kTile] = Mr;
         L[rt] += sum;
@@ -246,12 +211,11 @@ __device__ __forceinline__ void clear_state(float (&M)[NRT], float (&L)[NRT], f3
 }
 
 // ---- 1. the sweep: the chunk's K and V once, online softmax, P.V ----------
-// pre() runs once per wave with each wave's first tile already in flight.
-template <int NRT, bool kStream, bool kPaged, typename Codec, typename Pre>
+template <int NRT, bool kStream, bool kPaged>
 __device__ __forceinline__ void sweep_chunk(const VerifyArgs& a, const Chunk& k, const Rows<NRT>& r,
-                                            typename Codec::T* stash, int stride, float* mtile,
+                                            float* stash, int stride, float* mtile,
                                             int mts, float (&M)[NRT], float (&L)[NRT],
-                                            f32x4 (&oacc)[8][NRT], Pre&& pre) {
+                                            f32x4 (&oacc)[8][NRT]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m16 = lane & 15, G = lane >> 4;
     const size_t cache_off = (size_t)k.unit * a.max_ctx * kHeadDim;
@@ -266,10 +230,9 @@ __device__ __forceinline__ void sweep_chunk(const VerifyArgs& a, const Chunk& k,
                                           k.c, k.key_begin + t * kTile, k.T, m16, G, bf);
         },
         [&](const KVTile& bf, int t) {
-            fused_tile<NRT, Codec>(a, r, bf, k.key_begin + t * kTile, t * kTile, stash, stride, mtile,
-                                   mts, m16, G, M, L, oacc);
-        },
-        pre);
+            fused_tile<NRT>(a, r, bf, k.key_begin + t * kTile, t * kTile, stash, stride, mtile, mts, m16,
+                            G, M, L, oacc);
+        });
 }
 
 // ---- 2. publish the chunk's partial output, then its row statistics ------
@@ -461,14 +424,15 @@ __device__ __forceinline__ void row_sums(const VerifyArgs& a, const Chunk& k, co
 // Every thread calls this.  Waits for every chunk's statistics of the unit
 // (false: the wait gave up, reported on the status word; nothing written),
 // then writes the scores of the chunk's keys from its stash and the outputs
-// of rows s, s + nchunk, ... (kDefer: the caller runs row_sums later).  With
+// of rows s, s + nchunk, ... (kStep: the caller runs row_sums later).  With
 // kStep the score bits also go to skeys.
-template <int NRT, typename Codec, bool kStep, int kPoll = 8, int kSum = 4, bool kDefer = false>
+template <int NRT, bool kStep>
 __device__ __forceinline__ bool finish_chunk(const FusedArgs& fa, const Chunk& k, uint64_t want,
-                                             bool clean, typename Codec::T* stash, int stride,
+                                             bool clean, float* stash, int stride,
                                              const float* mtile, int mts, float* row_lse,
                                              int* wait_failed, uint32_t* skeys) {
     const VerifyArgs& a = fa.v;
+    constexpr int kPoll = 8, kSum = 4;   // chunks per lane per poll; per thread per row-sum pass
     const int tid = threadIdx.x, lane = tid & 63;
     const int R = k.R, nchunk = k.nchunk, slot0 = k.slot0;
     const uint64_t tag_hi = (want & 0xFFFFFFFFull) << 32;
@@ -533,11 +497,11 @@ __device__ __forceinline__ bool finish_chunk(const FusedArgs& fa, const Chunk& k
 
     // The first chunks of this workgroup's first row in step 4 (all of them
     // for up to 32 chunks), loaded now so that the round trip overlaps 3b
-    // (kDefer: step 4 is left to the caller).
+    // (kStep: step 4 is left to the caller).
     const int d4 = tid & 31, sg = tid >> 5;
     f32x4 pv[kSum];
     float pm[kSum];
-    if (!kDefer && k.s < R) load_part<kSum>(a, k, k.s, sg, d4, pv, pm);
+    if (!kStep && k.s < R) load_part<kSum>(a, k, k.s, sg, d4, pv, pm);
 
     const int nk = k.key_end - k.key_begin;
 
@@ -559,7 +523,7 @@ __device__ __forceinline__ bool finish_chunk(const FusedArgs& fa, const Chunk& k
             for (int hh = 0; hh < a.group; ++hh) {
                 f32x4 sc = {0.f, 0.f, 0.f, 0.f};
                 for (int row = r0 + hh; row < R; row += a.group)
-                    sc += Codec::get4(stash + row * stride, k4) * fast_exp2(mt[row * mts] - row_lse[row]);
+                    sc += *reinterpret_cast<const f32x4*>(stash + row * stride + k4) * fast_exp2(mt[row * mts] - row_lse[row]);
                 float* hrow = a.scores + ((size_t)k.b * a.n_q_heads + k.c * a.group + hh) * a.max_ctx;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -575,7 +539,7 @@ __device__ __forceinline__ bool finish_chunk(const FusedArgs& fa, const Chunk& k
                 float cr[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    pr[j] = Codec::get4(stash + (row + j) * stride, k4);
+                    pr[j] = *reinterpret_cast<const f32x4*>(stash + (row + j) * stride + k4);
                     cr[j] = mt[(row + j) * mts] - row_lse[row + j];
                 }
 #pragma unroll
@@ -586,14 +550,14 @@ __device__ __forceinline__ bool finish_chunk(const FusedArgs& fa, const Chunk& k
                 float cr[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    pr[j] = Codec::get4(stash + (row + j) * stride, k4);
+                    pr[j] = *reinterpret_cast<const f32x4*>(stash + (row + j) * stride + k4);
                     cr[j] = fast_exp2(mt[(row + j) * mts] - row_lse[row + j]);
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) sc += pr[j] * cr[j];
             }
             for (; row < R; ++row)
-                sc += Codec::get4(stash + row * stride, k4) * fast_exp2(mt[row * mts] - row_lse[row]);
+                sc += *reinterpret_cast<const f32x4*>(stash + row * stride + k4) * fast_exp2(mt[row * mts] - row_lse[row]);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (k4 + i < nk) srow[k.key_begin + k4 + i] = sc[i];
@@ -602,7 +566,7 @@ __device__ __forceinline__ bool finish_chunk(const FusedArgs& fa, const Chunk& k
     }
 
     // ---- 4. rows s, s + nchunk, ... summed over the unit's chunks ----------
-    if constexpr (!kDefer) {
+    if constexpr (!kStep) {
         __syncthreads();   // the stash is free once every thread's scores are out
         row_sums<kSum>(a, k, row_lse, reinterpret_cast<f32x4*>(stash), &pv, &pm);
     }
@@ -630,7 +594,7 @@ __global__ __launch_bounds__(kThreads) void verify_fused_kernel(FusedArgs fa) {
 
     const Chunk k = chunk_of(a, blockIdx.x);
     const int chunk = a.chunk;
-    const int stride = chunk + StashF32::kPad;
+    const int stride = chunk + kStashPad;
     const int mts = chunk / kTile;
     float* mtile = stash + NRT * 16 * stride;   // [NRT*16][mts] reference row maxima per tile
     float* park = mtile + mts * (NRT * 16);     // [2][16][kParkStride]
@@ -642,15 +606,14 @@ __global__ __launch_bounds__(kThreads) void verify_fused_kernel(FusedArgs fa) {
     float M[NRT], L[NRT];
     f32x4 oacc[8][NRT];
     clear_state<NRT>(M, L, oacc);
-    sweep_chunk<NRT, kStream, kPaged, StashF32>(a, k, r, stash, stride, mtile, mts, M, L, oacc, [] {});
+    sweep_chunk<NRT, kStream, kPaged>(a, k, r, stash, stride, mtile, mts, M, L, oacc);
     bool clean;
     const uint64_t want = publish_chunk<NRT>(fa, k, M, L, oacc, wml, park, &wait_failed, &clean);
     // (decode step: the chunk's score bits also go to skeys, in the parking
     // slices, free once the partial output is out)
     uint32_t* skeys = reinterpret_cast<uint32_t*>(park);
     // (decode step: the output rows are summed later, see below)
-    if (!finish_chunk<NRT, StashF32, kStep, 8, 4, kStep>(fa, k, want, clean, stash, stride, mtile, mts,
-                                                         row_lse, &wait_failed, skeys))
+    if (!finish_chunk<NRT, kStep>(fa, k, want, clean, stash, stride, mtile, mts, row_lse, &wait_failed, skeys))
         return;
     if constexpr (kStep) {
         // ---- 5. select (Eq. 4) and the first draft step (Eq. 5) ------------
@@ -680,112 +643,10 @@ __global__ __launch_bounds__(kThreads) void verify_fused_kernel(FusedArgs fa) {
     chunk0_done(fa, k);
 }
 
-// Chunks per lane per statistics poll, and per thread per row-sum pass, in
-// the persistent kernel's finish (its units may have more chunks).
-constexpr int kPipePoll = 16, kPipeSum = 8;
-
-// Persistent one-sweep kernel (16-bit stash, two chunk buffers): workgroup w
-// takes chunks w, w + G, w + 2G, ... (round j: its chunk w + jG; G = the grid,
-// all resident at once).  At the start of round j + 1's sweep, with each
-// wave's first tile of it in flight, the workgroup publishes its round-j chunk
-// and finishes its round j - 1 chunk (whose stash buffer the new sweep then
-// fills), so each chunk's exchange runs a round behind its streaming.  The
-// host keeps a unit's chunks within two consecutive rounds (at most G per
-// unit), so that finish waits only for chunks of rounds j - 1 and j, which
-// every workgroup publishes at the start of rounds j and j + 1, before it
-// waits on anything there: no wait depends on a workgroup that is itself
-// waiting.
-template <int NRT, bool kPaged>
-__global__ __launch_bounds__(kThreads) void verify_pipe_kernel(FusedArgs fa) {
-    using Codec = StashU16;
-    const VerifyArgs& a = fa.v;
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    __shared__ float2 wml[kWaves][NRT * 16];
-    __shared__ float row_lse[kRowCap];
-    __shared__ int wait_failed;
-
-    const int chunk = a.chunk;
-    const int stride = chunk + Codec::kPad;
-    const int mts = chunk / kTile;
-    const int code_bytes = NRT * 16 * stride * 2;                 // a multiple of 16
-    const int buf_bytes = code_bytes + NRT * 16 * mts * 4;
-    char* base = reinterpret_cast<char*>(lds);
-    float* park = reinterpret_cast<float*>(base + 2 * buf_bytes);   // [2][16][kParkStride]
-    auto codes = [&](int j) { return reinterpret_cast<uint16_t*>(base + (j & 1) * buf_bytes); };
-    auto tiles = [&](int j) { return reinterpret_cast<float*>(base + (j & 1) * buf_bytes + code_bytes); };
-    const int lane = threadIdx.x & 63;
-    const int m16 = lane & 15, G = lane >> 4;
-    const int grid = gridDim.x, w = blockIdx.x;
-    const int n = (fa.n_tasks - w + grid - 1) / grid;   // >= 1: the grid is at most the task count
-
-    float M[NRT], L[NRT];
-    f32x4 oacc[8][NRT];
-    clear_state<NRT>(M, L, oacc);
-    Chunk k1 = chunk_of(a, w), k2 = k1;   // chunks j - 1 and j - 2
-    uint64_t want1 = 0, want2 = 0;
-    bool clean1 = false, clean2 = false, failed = false;
-    // (the finish calls are written out: a lambda around them is not inlined
-    // and puts the kernel's locals on the scratch stack)
-    for (int j = 0; j < n; ++j) {
-        const Chunk k = chunk_of(a, w + j * grid);
-        Rows<NRT> r;
-        load_rows<NRT>(a, k.b, k.c, k.T, k.nq, 0, k.nq, m16, G, r);
-        sweep_chunk<NRT, false, kPaged, Codec>(a, k, r, codes(j), stride, tiles(j), mts, M, L, oacc, [&] {
-            if (j >= 1) {
-                want1 = publish_chunk<NRT>(fa, k1, M, L, oacc, wml, park, &wait_failed, &clean1);
-                clear_state<NRT>(M, L, oacc);
-            }
-            if (j >= 2) {   // chunk j - 2's stash: buffer (j - 2) & 1 = j & 1
-                if (finish_chunk<NRT, Codec, false, kPipePoll, kPipeSum>(fa, k2, want2, clean2, codes(j), stride,
-                                                                         tiles(j), mts, row_lse,
-                                                                         &wait_failed, nullptr))
-                    chunk0_done(fa, k2);
-                else
-                    failed = true;
-            }
-        });
-        if (failed) return;
-        k2 = k1;
-        want2 = want1;
-        clean2 = clean1;
-        k1 = k;
-    }
-    want1 = publish_chunk<NRT>(fa, k1, M, L, oacc, wml, park, &wait_failed, &clean1);
-    if (n >= 2) {
-        if (!finish_chunk<NRT, Codec, false, kPipePoll, kPipeSum>(fa, k2, want2, clean2, codes(n), stride, tiles(n),
-                                                                  mts, row_lse, &wait_failed, nullptr))
-            return;
-        chunk0_done(fa, k2);
-    }
-    if (!finish_chunk<NRT, Codec, false, kPipePoll, kPipeSum>(fa, k1, want1, clean1, codes(n - 1), stride,
-                                                              tiles(n - 1), mts, row_lse, &wait_failed,
-                                                              nullptr))
-        return;
-    chunk0_done(fa, k1);
-}
-
 template <int NRT>
 constexpr size_t fused_lds_bytes(int chunk) {
     // the probability stash with its tile maxima, then the parking slices
-    return ((size_t)NRT * 16 * (chunk + StashF32::kPad + chunk / kTile) + kParkFloats) * sizeof(float);
-}
-
-constexpr int kPipeMaxRowTiles = 3;   // 48 rows: more spill the persistent kernel's registers
-
-template <int NRT>
-constexpr size_t pipe_lds_bytes(int chunk) {
-    // two buffers of 16-bit codes and tile maxima, then the parking slices
-    const size_t codes = (size_t)NRT * 16 * (chunk + StashU16::kPad) * 2;
-    const size_t tiles = (size_t)NRT * 16 * (chunk / kTile) * sizeof(float);
-    return 2 * (codes + tiles) + kParkFloats * sizeof(float);
-}
-
-// The largest chunk (a multiple of 128 keys) whose two buffers fit in LDS.
-template <int NRT>
-constexpr int max_pipe_chunk() {
-    int c = 128;
-    while (pipe_lds_bytes<NRT>(c + 128) + static_lds_bytes<NRT>() + 1024 <= 160 * 1024) c += 128;
-    return c;
+    return ((size_t)NRT * 16 * (chunk + kStashPad + chunk / kTile) + kParkFloats) * sizeof(float);
 }
 
 // Once per device and row-tile count: the kernels' dynamic LDS limits are
@@ -793,13 +654,13 @@ constexpr int max_pipe_chunk() {
 // holds at that LDS use are read (doing this twice is harmless, so a race
 // between threads is too).
 struct FusedDevice {
-    int n_cu, per_cu, pipe_per_cu;
+    int n_cu, per_cu;
 };
 
 template <int NRT>
 hipError_t fused_setup(FusedDevice* out) {
     constexpr int kMaxDevices = 64;
-    // packed (n_cu * 16 + per_cu) * 16 + pipe_per_cu, plus 1; 0: not set up yet
+    // packed n_cu * 16 + per_cu, plus 1; 0: not set up yet
     static std::atomic<int> state[kMaxDevices];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -817,30 +678,17 @@ hipError_t fused_setup(FusedDevice* out) {
             e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
         }
-        int cu = 0, blocks = 0, pipe_blocks = 0;
-        if constexpr (NRT <= kPipeMaxRowTiles) {
-            const int pipe_lds = (int)pipe_lds_bytes<NRT>(max_pipe_chunk<NRT>());
-            const void* pfns[2] = {reinterpret_cast<const void*>(verify_pipe_kernel<NRT, false>),
-                                   reinterpret_cast<const void*>(verify_pipe_kernel<NRT, true>)};
-            for (const void* f : pfns) {
-                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, pipe_lds);
-                if (e != hipSuccess) return e;
-            }
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&pipe_blocks, verify_pipe_kernel<NRT, false>,
-                                                             kThreads, pipe_lds);
-            if (e != hipSuccess) return e;
-        }
+        int cu = 0, blocks = 0;
         e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, verify_fused_kernel<NRT, true, false, false>,
                                                          kThreads, lds);
         if (e != hipSuccess) return e;
-        st = (std::min(cu, (1 << 20) - 1) * 16 + std::min(blocks, 15)) * 16 + std::min(pipe_blocks, 15) + 1;
+        st = std::min(cu, (1 << 20) - 1) * 16 + std::min(blocks, 15) + 1;
         if (dev >= 0 && dev < kMaxDevices) state[dev].store(st, std::memory_order_relaxed);
     }
-    out->n_cu = (st - 1) / 256;
-    out->per_cu = ((st - 1) / 16) % 16;
-    out->pipe_per_cu = (st - 1) % 16;
+    out->n_cu = (st - 1) / 16;
+    out->per_cu = (st - 1) % 16;
     return hipSuccess;
 }
 
@@ -851,18 +699,6 @@ hipError_t launch_fused_nrt(const FusedArgs& a, int n_slots, hipStream_t stream)
     if (e != hipSuccess) return e;
     const bool paged = a.v.block_table != nullptr;
     const dim3 grid(n_slots), block(kThreads);
-    if (a.n_tasks > 0) {   // persistent: n_slots workgroups over n_tasks chunks
-        if constexpr (NRT <= kPipeMaxRowTiles) {
-            const size_t dyn = pipe_lds_bytes<NRT>(a.v.chunk);
-            if (paged)
-                hipLaunchKernelGGL((verify_pipe_kernel<NRT, true>), grid, block, dyn, stream, a);
-            else
-                hipLaunchKernelGGL((verify_pipe_kernel<NRT, false>), grid, block, dyn, stream, a);
-            return hipGetLastError();
-        } else {
-            return hipErrorInvalidValue;   // (the host plans it only up to kPipeMaxRowTiles)
-        }
-    }
     // non-temporal K/V loads when every workgroup runs in the first round
     const bool stream1 = n_slots <= fd.n_cu;
     if (a.step) {   // (dense caches only; the host checks)
@@ -890,10 +726,10 @@ hipError_t launch_fused_nrt(const FusedArgs& a, int n_slots, hipStream_t stream)
 
 template <int NRT>
 FusedDevice fused_device() {
-    FusedDevice fd = {0, 0, 0};
+    FusedDevice fd = {0, 0};
     if (fused_setup<NRT>(&fd) != hipSuccess) {
         (void)hipGetLastError();
-        return FusedDevice{0, 0, 0};
+        return FusedDevice{0, 0};
     }
     return fd;
 }
@@ -915,25 +751,6 @@ int fused_blocks_per_cu(int row_tiles) {
         case 2: return fused_device<2>().per_cu;
         case 3: return fused_device<3>().per_cu;
         default: return fused_device<4>().per_cu;
-    }
-}
-
-int pipe_max_chunk(int row_tiles) {
-    static_assert(kPipeMaxRowTiles == 3, "the cases below");
-    switch (row_tiles) {
-        case 1: return max_pipe_chunk<1>();
-        case 2: return max_pipe_chunk<2>();
-        case 3: return max_pipe_chunk<3>();
-        default: return 0;   // not built for more rows
-    }
-}
-
-int pipe_blocks_per_cu(int row_tiles) {
-    switch (row_tiles) {
-        case 1: return fused_device<1>().pipe_per_cu;
-        case 2: return fused_device<2>().pipe_per_cu;
-        case 3: return fused_device<3>().pipe_per_cu;
-        default: return fused_device<4>().pipe_per_cu;
     }
 }
 

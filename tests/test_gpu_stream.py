@@ -1,0 +1,118 @@
+"""GPU parity of the streaming one-sweep verify kernel (two workgroups per CU;
+verify_stream.hip) at the edges of its tiles and chunks.
+
+Both stash forms: 16-bit codes (reached with a small CU budget, so that small
+shapes take several chunks per unit) and fp32 (contexts of more than 64 code
+chunks per head).  Outputs and scores are held to the oracle bars; the fp32
+form's scores, sums of fp32 probabilities, to 1e-5."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_common import Dev, abs_v, check_outputs, check_score_mass, check_scores, params_of
+from paper_2607_27735_amd import binding as B
+from paper_2607_27735_amd.workloads import bf16_bits_to_f32, f32_to_bf16_bits, generate
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU visible", allow_module_level=True)
+
+NAN_BF16 = np.uint16(0x7FC0)
+
+
+def _poison(w):
+    for b in range(w.batch):
+        w.k[b, :, w.ctx_len[b]:] = NAN_BF16
+        w.v[b, :, w.ctx_len[b]:] = NAN_BF16
+        w.q[b, w.q_len[b]:] = NAN_BF16
+    return w
+
+
+def _gen(seed, ctx, ql, hq, hkv, spare=3):
+    return _poison(generate(seed, name="stream", batch=len(ctx), n_q_heads=hq, n_kv_heads=hkv,
+                            ctx_len=ctx, q_len=ql, max_ctx=max(ctx) + spare, max_q=max(ql),
+                            budget=64, heavy_hitters=0))
+
+
+def _ramp(w, top):
+    """Every key's logits rise along the context to about `top` (log2 units):
+    the reference maxima move again and again."""
+    for b in range(w.batch):
+        T = int(w.ctx_len[b])
+        for c in range(w.n_kv_heads):
+            rows = bf16_bits_to_f32(w.q[b, :w.q_len[b], c * w.group:(c + 1) * w.group]).reshape(-1, 128)
+            u = rows.mean(axis=0).astype(np.float64)
+            u /= u @ u                      # one unit of the mean query's product
+            k = bf16_bits_to_f32(w.k[b, c, :T]).astype(np.float64) * 0.2
+            k += (np.arange(T)[:, None] / T) * (top / (w.sm_scale * 1.4427)) * u
+            w.k[b, c, :T] = f32_to_bf16_bits(k.astype(np.float32))
+    return w
+
+
+# name: (workload, CU budget or 0, 16-bit codes?)
+CASES = {
+    # one and two keys past a tile and a chunk; 12 rows; single-chunk units; T below a tile
+    "codes-rows12": (lambda: _gen(801, [4097, 1057, 31, 2050], [3, 3, 1, 2], 8, 2), 5, True),
+    # 17 and 31 rows (a second row tile begun and nearly full), group not a power of two
+    "codes-group31": (lambda: _gen(802, [2500, 1601], [1, 1], 31, 1), 4, True),
+    "codes-rows17": (lambda: _gen(803, [2500, 1], [17, 1], 1, 1), 4, True),
+    # 33 rows, logits that rise by 120 octaves
+    "codes-ramp33": (lambda: _ramp(_gen(804, [3000, 1500], [11, 5], 6, 2), 120.0), 6, True),
+    # fp32: ragged long contexts, 40, 8 and 36 rows
+    "fp32-rows40": (lambda: _gen(805, [44999, 300, 20001], [10, 2, 9], 16, 4), 0, False),
+    # fp32, logits that rise by 120 octaves: stashed probabilities are rescaled
+    "fp32-ramp40": (lambda: _ramp(_gen(806, [45056], [10], 16, 4), 120.0), 0, False),
+}
+
+
+@pytest.fixture(autouse=True)
+def _reset():
+    torch.cuda.synchronize()
+    B.exchange_status()
+    yield
+    B.set_cu_budget(0)
+
+
+@pytest.mark.parametrize("per_head", [False, True])
+@pytest.mark.parametrize("name", list(CASES))
+def test_stream_matches_oracle(name, per_head):
+    make, budget, codes = CASES[name]
+    w = make()
+    print(f"[stream] {name} {w.describe()} per_head={per_head}", flush=True)
+    d = Dev(w)
+    B.set_cu_budget(budget)
+    p = B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=True, per_head=per_head)
+    sch, chunk, items = B.verify_plan(B.verify_shape(d.q, d.k), p, w.ctx_len, w.q_len)
+    assert sch == B.VERIFY_ONE_SWEEP_PERSISTENT, (sch, chunk, items)
+    heads = w.n_q_heads if per_head else w.n_kv_heads
+    out = torch.full(d.q.shape, -7.0, dtype=torch.float32, device="cuda")
+    sc = torch.full((w.batch, heads, w.max_ctx), -1.0, dtype=torch.float32, device="cuda")
+    B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, out=out, scores=sc)
+    torch.cuda.synchronize()
+    assert B.exchange_status() == 0
+    o, s = out.double().cpu().numpy(), sc.double().cpu().numpy()
+    o_ref, s_ref = oracle.verify(w)
+    if per_head:
+        s_ref = oracle.head_scores(w)
+    mask = np.arange(w.max_q)[None, :, None] < w.q_len[:, None, None] * np.ones((1, 1, w.n_q_heads), bool)
+    oabs, _ = oracle.verify(w, v=abs_v(w))
+    check_outputs(o, o_ref, oabs, mask)
+    assert np.all(o[~mask] == -7.0)
+    tol = 1e-3 if codes else 4.3e-5 if "ramp" in name else 1e-5
+    for b in range(w.batch):
+        T = int(w.ctx_len[b])
+        assert np.all(s[b, :, T:] == -1.0)
+        # every key within 1e-3 (codes) or 1e-5 (fp32) of its score; logits near 2^7 log2 units
+        # carry fp32 errors of a few ulps, 2^-16 each, so the ramp's probabilities one of
+        # 4 * 2^-16 * ln 2 = 4.3e-5; keys below 2^-40 of the largest score may be flushed relative
+        # to the reference maxima
+        r, g = s_ref[b, :, :T], s[b, :, :T]
+        big = r > r.max() * 2.0 ** -40
+        assert np.abs(g - r)[big].max() == 0 or (np.abs(g - r)[big] / r[big]).max() <= tol
+        assert np.all(g >= 0) and np.all(g[~big] <= r.max() * 2.0 ** -39)
+    if not per_head:
+        check_score_mass(s, w)
+    if "ramp" not in name:
+        check_scores(s, s_ref, w.ctx_len)
