@@ -1498,7 +1498,7 @@ int plan_logits(int32_t n_rows, int32_t vocab, LogitPlan* plan) {
     plan->part_off = kEpochBytes;
     plan->tag_off = plan->part_off + align_up(slots * 4 * sizeof(float));
     plan->argmax_off = plan->tag_off + align_up(slots * sizeof(uint64_t));
-    plan->bytes = plan->argmax_off + align_up((size_t)n_rows * sizeof(int32_t));
+    plan->bytes = plan->argmax_off + align_up((size_t)n_rows * sizeof(uint64_t));
     return SSL_OK;
 }
 
@@ -1590,7 +1590,11 @@ int ssl_greedy_accept(const void* logits, int32_t dtype, int32_t batch, int32_t 
     a.row_stride = row_stride;
     a.n_chunks = plan.n_chunks;
     a.entropy = nullptr;
-    a.argmax = reinterpret_cast<int32_t*>(ws + plan.argmax_off);
+    a.argmax = nullptr;
+    a.row_best = reinterpret_cast<uint64_t*>(ws + plan.argmax_off);
+    a.draft = draft_tokens;
+    a.n_accepted = n_accepted;
+    a.next_token = next_token;
     a.part = reinterpret_cast<float*>(ws + plan.part_off);
     a.tag = reinterpret_cast<uint64_t*>(ws + plan.tag_off);
     rc = epochs_if_captured(stream, ws, a.n_rows, &a.epoch);
@@ -1600,23 +1604,16 @@ int ssl_greedy_accept(const void* logits, int32_t dtype, int32_t batch, int32_t 
     a.call_tag = next_call_tag();
     a.rows_per_seq = max_k + 1;
     for (int b = 0; b < batch; ++b) a.k_len[b] = k_len_host[b];
-    if (const int hip_st = hip_rc(launch_logit_stats(a, dtype == SSL_DT_F32, stream))) return hip_st;
-    AcceptArgs c = {};
-    c.argmax = a.argmax;
-    c.draft = draft_tokens;
-    c.n_accepted = n_accepted;
-    c.next_token = next_token;
-    c.max_k = max_k;
-    for (int b = 0; b < batch; ++b) c.k_len[b] = k_len_host[b];
-    return hip_rc(launch_greedy_accept(c, batch, stream));
+    return hip_rc(launch_logit_stats(a, dtype == SSL_DT_F32, stream));
 }
 
 }  // extern "C"
 
 namespace {
 
-// Speculative sampling workspace: chunk and row statistics of the 2 max_k + 1
-// rows of every sequence, the picked positions and the chunk masses.
+// Speculative sampling workspace: chunk statistics of the 2 max_k + 1 rows of
+// every sequence, the picked positions with their rows' statistics, and the
+// chunk masses.
 struct SpecPlan {
     int n_chunks;
     size_t chunk_off, row_off, pick_off, mass_off, bytes;
@@ -1630,7 +1627,7 @@ int plan_spec(int32_t batch, int32_t max_k, int32_t vocab, SpecPlan* plan) {
     const size_t rows = (size_t)batch * (2 * max_k + 1);
     plan->chunk_off = kEpochBytes;
     plan->row_off = plan->chunk_off + align_up(rows * plan->n_chunks * sizeof(float2));
-    plan->pick_off = plan->row_off + align_up(rows * sizeof(float2));
+    plan->pick_off = plan->row_off + align_up((size_t)batch * 2 * sizeof(float2));
     plan->mass_off = plan->pick_off + align_up((size_t)batch * sizeof(int32_t));
     plan->bytes = plan->mass_off + align_up((size_t)batch * plan->n_chunks * sizeof(float2));
     return SSL_OK;

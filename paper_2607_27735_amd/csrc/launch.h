@@ -276,21 +276,18 @@ struct LogitArgs {
     uint64_t* epoch;        // [n_rows] exchange epochs (any initial value), or null
     uint64_t call_tag;
     Exchange xc;
-    int32_t rows_per_seq;   // acceptance: max_k + 1 (rows past k_len[b] + 1 skipped); else 0
-    int32_t k_len[kTableBatch];
-};
-
-struct AcceptArgs {
-    const int32_t* argmax;  // [batch][max_k + 1]
+    // Greedy acceptance (rows_per_seq = max_k + 1, else 0): rows past a
+    // sequence's k_len[b] + 1 are skipped, and its last row's workgroup compares
+    // the rows' argmax with the drafted tokens.
+    int32_t rows_per_seq;
+    uint64_t* row_best;     // [n_rows] tagged argmax of each row
     const int32_t* draft;   // [batch][max_k]
     int32_t* n_accepted;    // [batch]
     int32_t* next_token;    // [batch]
-    int32_t max_k;
     int32_t k_len[kTableBatch];
 };
 
 hipError_t launch_logit_stats(const LogitArgs& a, bool f32, hipStream_t stream);
-hipError_t launch_greedy_accept(const AcceptArgs& a, int batch, hipStream_t stream);
 
 // Speculative sampling.  Rows of sequence b: target rows 0..max_k of tlogits
 // ([batch][max_k + 1][row_stride]) and drafter rows 0..max_k-1 of dlogits
@@ -307,7 +304,7 @@ struct SpecArgs {
     int32_t* n_accepted;     // [batch]
     int32_t* next_token;     // [batch]
     float2* chunk_ms;        // [batch][2 max_k + 1][n_chunks] (max, sum) of x / tau per chunk
-    float2* row_ms;          // [batch][2 max_k + 1] the same per row
+    float2* row_ms;          // [batch][2] the same of target and drafter row `pick`
     int32_t* pick;           // [batch] the first failing position (or k)
     float2* mass;            // [batch][n_chunks] (residual, target) mass per chunk
     int32_t k_len[kTableBatch];

@@ -27,33 +27,67 @@ __device__ __forceinline__ int elem(int chunk, int q, int tid) {
     return (blk0 + (q / per) * kThreads + tid) * per + q % per;
 }
 
-// The 32 logits of thread tid in chunk `chunk` of the row at `row_base`
-// (bf16 or fp32), all loads in flight together; loads are clamped into the
-// row's last 16-byte block and elements at or past vocab read as -inf.
+// The 16-byte blocks of thread tid in chunk `chunk` of the row at `row_base`,
+// all loads in flight together; loads are clamped into the row's last block.
+template <bool kF32>
+__device__ __forceinline__ void load_blocks(const void* row_base, int vocab, int chunk, int tid,
+                                            uint4 (&raw)[loads<kF32>()]) {
+    constexpr int per = per_load<kF32>();
+    const int last_blk = (vocab - 1) / per;
+    const int blk0 = chunk * (kLogitChunk / per);
+    const char* base = static_cast<const char*>(row_base);
+#pragma unroll
+    for (int j = 0; j < loads<kF32>(); ++j) {
+        const int blk = min(blk0 + j * kThreads + tid, last_blk);
+        raw[j] = *reinterpret_cast<const uint4*>(base + (size_t)blk * 16);
+    }
+}
+
+// The logits of one block, the thread's load j; elements at or past vocab read
+// as -inf.
+template <bool kF32>
+__device__ __forceinline__ void unpack_block(const uint4& raw, int vocab, int chunk, int j, int tid,
+                                             float (&x)[per_load<kF32>()]) {
+    constexpr int per = per_load<kF32>();
+    const int i0 = (chunk * (kLogitChunk / per) + j * kThreads + tid) * per;
+    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+        const float v = kF32 ? __builtin_bit_cast(float, w[e])
+                             : ((e & 1) ? bf16_hi(w[e >> 1]) : bf16_lo(w[e >> 1]));
+        x[e] = i0 + e < vocab ? v : -INFINITY;
+    }
+}
+
+// Runs f(j, raw blocks of load j) for the thread's loads in order, as a loop:
+// the code of one block stays in the instruction cache, where the unrolled
+// kernel's would be fetched once and run once.  The blocks are passed down a
+// register queue, so that the loop needs no indexed registers.
+template <int kN, int kArrays, typename F>
+__device__ __forceinline__ void for_blocks(uint4 (&raw)[kArrays][kN], F&& f) {
+#pragma unroll 1
+    for (int j = 0; j < kN; ++j) {
+        f(j);
+#pragma unroll
+        for (int r = 0; r < kArrays; ++r)
+#pragma unroll
+            for (int q = 0; q + 1 < kN; ++q) raw[r][q] = raw[r][q + 1];
+    }
+}
+
+// The 32 logits of thread tid in chunk `chunk` of the row (bf16 or fp32).
 template <bool kF32>
 __device__ __forceinline__ void load_chunk(const void* row_base, int vocab, int chunk, int tid,
                                            float (&x)[32]) {
     constexpr int per = per_load<kF32>();
-    constexpr int nl = loads<kF32>();
-    const int last_blk = (vocab - 1) / per;
-    const int blk0 = chunk * (kLogitChunk / per);
-    const char* base = static_cast<const char*>(row_base);
-    uint4 raw[nl];
+    uint4 raw[loads<kF32>()];
+    load_blocks<kF32>(row_base, vocab, chunk, tid, raw);
 #pragma unroll
-    for (int j = 0; j < nl; ++j) {
-        const int blk = min(blk0 + j * kThreads + tid, last_blk);
-        raw[j] = *reinterpret_cast<const uint4*>(base + (size_t)blk * 16);
-    }
+    for (int j = 0; j < loads<kF32>(); ++j) {
+        float y[per];
+        unpack_block<kF32>(raw[j], vocab, chunk, j, tid, y);
 #pragma unroll
-    for (int j = 0; j < nl; ++j) {
-        const uint32_t w[4] = {raw[j].x, raw[j].y, raw[j].z, raw[j].w};
-#pragma unroll
-        for (int e = 0; e < per; ++e) {
-            const int i = (blk0 + j * kThreads + tid) * per + e;
-            const float v = kF32 ? __builtin_bit_cast(float, w[e])
-                                 : ((e & 1) ? bf16_hi(w[e >> 1]) : bf16_lo(w[e >> 1]));
-            x[j * per + e] = i < vocab ? v : -INFINITY;
-        }
+        for (int e = 0; e < per; ++e) x[j * per + e] = y[e];
     }
 }
 

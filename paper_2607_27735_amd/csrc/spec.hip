@@ -5,15 +5,20 @@
 // softmax(drafter row j / tau).  Drafted token x_j passes when
 // u_j q_j(x_j) < p_j(x_j); after the first failure (position m) the next
 // token is drawn by inversion from max(0, p_m - q_m), after k passes from p_k.
-// Five small launches, the kernel boundaries their only synchronisation:
+// Three launches, the kernel boundaries their only synchronisation:
 //   stats:  per (row, chunk of 8192 logits) the max of x / tau and the sum of
 //           e^(x / tau - max), for the target rows 0..k and drafter rows 0..k-1;
-//   rows:   per row, the chunks merged in a fixed order (one wave);
-//   decide: per sequence, lane j tests drafted token j; m = the first failure;
-//   mass:   per (sequence, chunk) the mass of the distribution drawn from
-//           (residual and plain target), summed in a fixed order;
+//   mass:   per (sequence, chunk) every row's chunks merged in a fixed tree,
+//           lane j tests drafted token j, m = the first failure, and the mass of
+//           the distribution drawn from (residual and plain target) in the
+//           chunk, summed in a fixed order;
 //   sample: per sequence, the chunk where the cumulative mass passes
 //           u * total, then a scan of that chunk in index order.
+// A call moves a few MB, so it is bound by its chain of dependent loads: the
+// row merges and the decision are a few KB and are redone by every chunk's
+// workgroup rather than given launches of their own, and the loads of a stage
+// go out together (4 sequences of 6 drafted tokens, 128256-token vocabulary,
+// bf16: 34.6 us of kernel time in five launches, 27.7 us in three).
 // Everything is fp32.  The chunk masses and the in-chunk scan add in
 // different orders; when rounding leaves the scan short of the target, the
 // chunk's last element with mass is drawn.
@@ -111,18 +116,6 @@ __global__ __launch_bounds__(kThreads) void spec_stats_kernel(SpecArgs a) {
     }
 }
 
-// ---- rows: one wave per (sequence, row) -------------------------------------------
-__global__ __launch_bounds__(kWave) void spec_rows_kernel(SpecArgs a) {
-    const int rows = 2 * a.max_k + 1;
-    const int b = blockIdx.x / rows, r = blockIdx.x - b * rows;
-    if (!row_needed(a, b, r)) return;
-    const int lane = threadIdx.x;
-    const size_t base = ((size_t)b * rows + r) * a.n_chunks;
-    const float2 v = lane < a.n_chunks ? a.chunk_ms[base + lane] : make_float2(-INFINITY, 0.f);
-    const float2 t = wave_ms(v);
-    if (lane == 0) a.row_ms[(size_t)b * rows + r] = t;
-}
-
 // p(x) for a row with merged (max, sum) ms at scaled logit y = x / tau.
 __device__ __forceinline__ float prob(float y, float2 ms) {
     return fast_exp2((y - ms.x) * kLog2e) / ms.y;
@@ -134,66 +127,105 @@ __device__ __forceinline__ float logit_at(const char* row, int i) {
     return bf16_lo((uint32_t)reinterpret_cast<const uint16_t*>(row)[i]);
 }
 
-// ---- decide: one wave per sequence ---------------------------------------------------
-template <bool kF32>
-__global__ __launch_bounds__(kWave) void spec_decide_kernel(SpecArgs a) {
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const int k = a.k_len[b], rows = 2 * a.max_k + 1;
-    bool pass = true;
-    if (lane < k) {
-        const int x = min(max(a.draft[(size_t)b * a.max_k + lane], 0), a.vocab - 1);
-        const float2 mt = a.row_ms[(size_t)b * rows + lane];
-        const float2 md = a.row_ms[(size_t)b * rows + a.max_k + 1 + lane];
-        const float p = prob(logit_at<kF32>(row_base(a, b, lane, kF32), x) * a.inv_tau, mt);
-        const float q = prob(logit_at<kF32>(row_base(a, b, a.max_k + 1 + lane, kF32), x) * a.inv_tau, md);
-        pass = a.u_acc[(size_t)b * a.max_k + lane] * q < p;
-    }
-    const uint64_t fail = __ballot(!pass);
-    const int m = fail ? __builtin_ctzll(fail) : k;
-    if (lane == 0) {
-        a.n_accepted[b] = m;
-        a.pick[b] = m;
+// The merged (max, sum) of every row of sequence b into rms[] (LDS), a wave per
+// row, eight rows' loads in flight; rows that are not needed are left alone.
+__device__ __forceinline__ void merge_rows(const SpecArgs& a, int b, float2* rms) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rows = 2 * a.max_k + 1;
+    const int c = min(lane, a.n_chunks - 1);
+    for (int r0 = wave; r0 < rows; r0 += 8 * kWaves) {
+        float2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = a.chunk_ms[((size_t)b * rows + min(r0 + u * kWaves, rows - 1)) * a.n_chunks + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int r = r0 + u * kWaves;
+            if (r >= rows || !row_needed(a, b, r)) continue;   // wave-uniform
+            const float2 t = wave_ms(lane < a.n_chunks ? v[u] : make_float2(-INFINITY, 0.f));
+            if (lane == 0) rms[r] = t;
+        }
     }
 }
 
-// The weights of thread tid's 32 elements of chunk `chunk`: with a residual
-// (m < k), max(0, p_m - q_m) in w and p_m in pw; else p_k in both.
+// The blocks that thread tid weighs in chunk `chunk`: target row m and, with a
+// residual (m < k), drafter row m.
 template <bool kF32>
-__device__ __forceinline__ void chunk_weights(const SpecArgs& a, int b, int m, int chunk, int tid,
-                                              float2 mt, float2 md, float (&w)[32], float (&pw)[32]) {
-    const bool resid = m < a.k_len[b];
-    float xt[32];
-    lc::load_chunk<kF32>(row_base(a, b, m, kF32), a.vocab, chunk, tid, xt);
-#pragma unroll
-    for (int q = 0; q < 32; ++q) pw[q] = xt[q] == -INFINITY ? 0.f : prob(xt[q] * a.inv_tau, mt);
-    if (resid) {
-        float xd[32];
-        lc::load_chunk<kF32>(row_base(a, b, a.max_k + 1 + m, kF32), a.vocab, chunk, tid, xd);
-#pragma unroll
-        for (int q = 0; q < 32; ++q)
-            w[q] = fmaxf(pw[q] - (xd[q] == -INFINITY ? 0.f : prob(xd[q] * a.inv_tau, md)), 0.f);
-    } else {
-#pragma unroll
-        for (int q = 0; q < 32; ++q) w[q] = pw[q];
+struct Weights {
+    static constexpr int kPer = lc::per_load<kF32>(), kLoads = lc::loads<kF32>();
+    uint4 raw[2][kLoads];
+    float2 mt, md;
+    bool resid;
+
+    __device__ __forceinline__ void load(const SpecArgs& a, int b, int m, int chunk, int tid) {
+        resid = m < a.k_len[b];
+        lc::load_blocks<kF32>(row_base(a, b, m, kF32), a.vocab, chunk, tid, raw[0]);
+        lc::load_blocks<kF32>(row_base(a, b, resid ? a.max_k + 1 + m : m, kF32), a.vocab, chunk, tid, raw[1]);
     }
-}
+    // The weights of the block at the head of the queue, the thread's load j:
+    // max(0, p_m - q_m) in w and p_m in pw, or p_k in both without a residual.
+    __device__ __forceinline__ void block(const SpecArgs& a, int chunk, int j, int tid, float (&w)[kPer],
+                                          float (&pw)[kPer]) const {
+        float xt[kPer], xd[kPer];
+        lc::unpack_block<kF32>(raw[0][0], a.vocab, chunk, j, tid, xt);
+        lc::unpack_block<kF32>(raw[1][0], a.vocab, chunk, j, tid, xd);
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            pw[e] = xt[e] == -INFINITY ? 0.f : prob(xt[e] * a.inv_tau, mt);
+            const float qd = xd[e] == -INFINITY ? 0.f : prob(xd[e] * a.inv_tau, md);
+            w[e] = resid ? fmaxf(pw[e] - qd, 0.f) : pw[e];
+        }
+    }
+};
 
 // ---- mass: grid (n_chunks, batch) -----------------------------------------------------
 template <bool kF32>
 __global__ __launch_bounds__(kThreads) void spec_mass_kernel(SpecArgs a) {
     const int chunk = blockIdx.x, b = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rows = 2 * a.max_k + 1;
-    const int m = a.pick[b];
-    const float2 mt = a.row_ms[(size_t)b * rows + m];
-    const float2 md = a.row_ms[(size_t)b * rows + a.max_k + 1 + min(m, a.max_k - 1)];
-    float w[32], pw[32];
-    chunk_weights<kF32>(a, b, m, chunk, tid, mt, md, w, pw);
-    float s = 0.f, sp = 0.f;
-#pragma unroll
-    for (int q = 0; q < 32; ++q) {
-        s += w[q];
-        sp += pw[q];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k = a.k_len[b];
+    __shared__ float2 rms[2 * kAcceptMaxK + 1];
+    __shared__ int sh_m;
+    // drafted token j's logits in both rows, its uniform (lane j of wave 0)
+    float xt = 0.f, xd = 0.f, u = 0.f;
+    if (wave == 0 && lane < k) {
+        const int x = min(max(a.draft[(size_t)b * a.max_k + lane], 0), a.vocab - 1);
+        u = a.u_acc[(size_t)b * a.max_k + lane];
+        xt = logit_at<kF32>(row_base(a, b, lane, kF32), x);
+        xd = logit_at<kF32>(row_base(a, b, a.max_k + 1 + lane, kF32), x);
     }
+    merge_rows(a, b, rms);
+    __syncthreads();
+    if (wave == 0) {
+        const float p = prob(xt * a.inv_tau, rms[lane]);
+        const float q = prob(xd * a.inv_tau, rms[a.max_k + 1 + min(lane, a.max_k - 1)]);
+        const bool pass = lane >= k || u * q < p;
+        const uint64_t fail = __ballot(!pass);
+        if (lane == 0) sh_m = fail ? __builtin_ctzll(fail) : k;
+    }
+    __syncthreads();
+    const int m = sh_m;
+    const float2 mt = rms[m];
+    const float2 md = m < k ? rms[a.max_k + 1 + m] : make_float2(0.f, 1.f);   // (a row past k is not there)
+    if (chunk == 0 && tid == 0) {
+        a.n_accepted[b] = m;
+        a.pick[b] = m;
+        a.row_ms[2 * b] = mt;
+        a.row_ms[2 * b + 1] = md;
+    }
+    Weights<kF32> wt;
+    wt.mt = mt;
+    wt.md = md;
+    wt.load(a, b, m, chunk, tid);
+    float s = 0.f, sp = 0.f;
+    lc::for_blocks(wt.raw, [&](int j) {
+        float w[wt.kPer], pw[wt.kPer];
+        wt.block(a, chunk, j, tid, w, pw);
+#pragma unroll
+        for (int e = 0; e < wt.kPer; ++e) {
+            s += w[e];
+            sp += pw[e];
+        }
+    });
     s = wave_sum(s);
     sp = wave_sum(sp);
     __shared__ float2 wv[kWaves];
@@ -214,30 +246,34 @@ __global__ __launch_bounds__(kThreads) void spec_mass_kernel(SpecArgs a) {
 template <bool kF32>
 __global__ __launch_bounds__(kThreads) void spec_sample_kernel(SpecArgs a) {
     const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rows = 2 * a.max_k + 1;
-    const int m = a.pick[b];
-    const float2 mt = a.row_ms[(size_t)b * rows + m];
-    const float2 md = a.row_ms[(size_t)b * rows + a.max_k + 1 + min(m, a.max_k - 1)];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     __shared__ int sh_chunk, sh_use_p, sh_found, sh_last;
     __shared__ float sh_target;
     __shared__ float wtot[kWaves];
-    if (tid == 0) {
+    const int m = a.pick[b];
+    const float2 mt = a.row_ms[2 * b], md = a.row_ms[2 * b + 1];
+    if (wave == 0) {
         // the residual when it has mass, else the plain target row; the chunk
-        // where the cumulative mass (chunk order) passes u * total
+        // where the cumulative mass (chunk order) passes u * total.  Lane c
+        // holds chunk c's masses; the sums run in chunk order, wave-uniform.
+        const float2 v = a.mass[(size_t)b * a.n_chunks + min(lane, a.n_chunks - 1)];
+        const float usmp = a.u_smp[b];
+        auto at = [&](float x, int c) {
+            return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), c));
+        };
         float tot = 0.f, totp = 0.f;
         for (int c = 0; c < a.n_chunks; ++c) {
-            const float2 v = a.mass[(size_t)b * a.n_chunks + c];
-            tot += v.x;
-            totp += v.y;
+            tot += at(v.x, c);
+            totp += at(v.y, c);
         }
         const bool use_p = !(tot > 0.f);
+        const float mine = use_p ? v.y : v.x;
         const float total = use_p ? totp : tot;
-        const float target = a.u_smp[b] * total;
+        const float target = usmp * total;
         float run = 0.f;
         int cstar = -1, last = 0;
         for (int c = 0; c < a.n_chunks; ++c) {
-            const float2 v = a.mass[(size_t)b * a.n_chunks + c];
-            const float mc = use_p ? v.y : v.x;
+            const float mc = at(mine, c);
             if (mc > 0.f) last = c;
             if (cstar < 0 && run + mc > target) cstar = c;
             if (cstar < 0) run += mc;
@@ -245,39 +281,40 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(SpecArgs a) {
         if (cstar < 0) {   // rounding left the cumulative mass short: the last chunk with mass
             cstar = last;
             run = 0.f;
-            for (int c = 0; c < last; ++c) {
-                const float2 v = a.mass[(size_t)b * a.n_chunks + c];
-                run += use_p ? v.y : v.x;
-            }
+            for (int c = 0; c < last; ++c) run += at(mine, c);
         }
-        sh_chunk = cstar;
-        sh_use_p = use_p ? 1 : 0;
-        sh_target = target - run;
-        sh_found = 0x7fffffff;
-        sh_last = -1;
+        if (lane == 0) {
+            sh_chunk = cstar;
+            sh_use_p = use_p ? 1 : 0;
+            sh_target = target - run;
+            sh_found = 0x7fffffff;
+            sh_last = -1;
+        }
     }
     __syncthreads();
     const int chunk = sh_chunk;
     const float target = sh_target;
-    float w[32], pw[32];
-    chunk_weights<kF32>(a, b, m, chunk, tid, mt, md, w, pw);
-    if (sh_use_p) {
-#pragma unroll
-        for (int q = 0; q < 32; ++q) w[q] = pw[q];
-    }
+    Weights<kF32> wt;
+    wt.mt = mt;
+    wt.md = md;
+    wt.load(a, b, m, chunk, tid);
+    const bool use_p = sh_use_p != 0;
     // scan in index order: load j of every thread, thread by thread, then its
     // elements in order
-    constexpr int per = lc::per_load<kF32>();
-    constexpr int nl = lc::loads<kF32>();
     float carry = 0.f;
     int last = -1;
-#pragma unroll
-    for (int j = 0; j < nl; ++j) {
+    bool found = false;   // uniform
+    lc::for_blocks(wt.raw, [&](int j) {
+        if (found) return;
+        float w[wt.kPer], pw[wt.kPer];
+        wt.block(a, chunk, j, tid, w, pw);
+        const int i0 = lc::elem<kF32>(chunk, j * wt.kPer, tid);
         float s = 0.f;
 #pragma unroll
-        for (int e = 0; e < per; ++e) {
-            s += w[j * per + e];
-            if (w[j * per + e] > 0.f) last = lc::elem<kF32>(chunk, j * per + e, tid);
+        for (int e = 0; e < wt.kPer; ++e) {
+            w[e] = use_p ? pw[e] : w[e];
+            s += w[e];
+            if (w[e] > 0.f) last = i0 + e;
         }
         const float incl = wave_incl_scan_f(s);
         if (lane == kWave - 1) wtot[wave] = incl;
@@ -291,15 +328,15 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(SpecArgs a) {
         float run = before + incl - s;
         int cand = 0x7fffffff;
 #pragma unroll
-        for (int e = 0; e < per; ++e) {
-            run += w[j * per + e];
-            if (cand == 0x7fffffff && run > target) cand = lc::elem<kF32>(chunk, j * per + e, tid);
+        for (int e = 0; e < wt.kPer; ++e) {
+            run += w[e];
+            if (cand == 0x7fffffff && run > target) cand = i0 + e;
         }
         if (cand != 0x7fffffff) atomicMin(&sh_found, cand);
         __syncthreads();
         carry = all;
-        if (sh_found != 0x7fffffff) break;   // uniform: read after the barrier
-    }
+        found = sh_found != 0x7fffffff;   // read after the barrier
+    });
     if (last >= 0) atomicMax(&sh_last, last);
     __syncthreads();
     if (tid == 0) a.next_token[b] = sh_found != 0x7fffffff ? sh_found : max(sh_last, 0);
@@ -308,20 +345,15 @@ __global__ __launch_bounds__(kThreads) void spec_sample_kernel(SpecArgs a) {
 }  // namespace
 
 hipError_t launch_spec_accept(const SpecArgs& a, int batch, bool f32, hipStream_t stream) {
-    const int rows = 2 * a.max_k + 1;
-    const dim3 block(kThreads);
-    if (f32)
-        hipLaunchKernelGGL(spec_stats_kernel<true>, dim3(a.n_chunks, batch * rows), block, 0, stream, a);
-    else
-        hipLaunchKernelGGL(spec_stats_kernel<false>, dim3(a.n_chunks, batch * rows), block, 0, stream, a);
-    hipLaunchKernelGGL(spec_rows_kernel, dim3(batch * rows), dim3(kWave), 0, stream, a);
+    const dim3 block(kThreads), per_chunk(a.n_chunks, batch);
+    const dim3 per_row(a.n_chunks, batch * (2 * a.max_k + 1));
     if (f32) {
-        hipLaunchKernelGGL(spec_decide_kernel<true>, dim3(batch), dim3(kWave), 0, stream, a);
-        hipLaunchKernelGGL(spec_mass_kernel<true>, dim3(a.n_chunks, batch), block, 0, stream, a);
+        hipLaunchKernelGGL(spec_stats_kernel<true>, per_row, block, 0, stream, a);
+        hipLaunchKernelGGL(spec_mass_kernel<true>, per_chunk, block, 0, stream, a);
         hipLaunchKernelGGL(spec_sample_kernel<true>, dim3(batch), block, 0, stream, a);
     } else {
-        hipLaunchKernelGGL(spec_decide_kernel<false>, dim3(batch), dim3(kWave), 0, stream, a);
-        hipLaunchKernelGGL(spec_mass_kernel<false>, dim3(a.n_chunks, batch), block, 0, stream, a);
+        hipLaunchKernelGGL(spec_stats_kernel<false>, per_row, block, 0, stream, a);
+        hipLaunchKernelGGL(spec_mass_kernel<false>, per_chunk, block, 0, stream, a);
         hipLaunchKernelGGL(spec_sample_kernel<false>, dim3(batch), block, 0, stream, a);
     }
     return hipGetLastError();
