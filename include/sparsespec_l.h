@@ -76,8 +76,8 @@
  *    idx) is not validated: index values outside [0, max_ctx) are clamped
  *    (results are then meaningless but memory stays in bounds).
  *  - Limits: head_dim 128; 1 <= batch <= 64; max_q <= 64; group <= 64 for
- *    verify (more than 64 rows per KV head, q_len * group > 64, run the
- *    two-sweep schedule once per block of 64 / group positions);
+ *    verify (more than 64 rows per KV head, q_len * group > 64, run in
+ *    row blocks, see ssl_verify_attn);
  *    n_q_heads / n_kv_heads <= 16 for the draft call.
  */
 #ifndef SPARSESPEC_L_H
@@ -235,10 +235,11 @@ int32_t ssl_index_count(int32_t T, int32_t k_sink, int32_t k_recent, int32_t bud
  * SSL_ERR_UNSUPPORTED if head_dim != 128, batch > 64, group > 64, or a
  * one-sweep request that does not fit (including any with q_len * group >
  * 64).  When a KV head has more than 64 verify rows (e.g. Eq. 3 seeded over
- * the last W = 16 prompt positions of a group of 8), the call runs the
+ * the last W = 16 prompt positions of a group of 8), the call runs either the
  * two-sweep schedule once per block of 64 / group positions, last positions
- * first, and adds the later blocks' scores to the first's.  The workspace
- * size covers both schedules.
+ * first, or one launch of the streaming form over blocks of at most 32 rows,
+ * whichever takes fewer rounds of workgroups; the later blocks' scores are
+ * added to the first's.  The workspace size covers both schedules.
  */
 int ssl_verify_workspace(const ssl_shape *shape, const ssl_params *params,
                          const int32_t *ctx_len_host, const int32_t *q_len_host,

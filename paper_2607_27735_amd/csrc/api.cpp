@@ -173,36 +173,42 @@ struct VerifyPlan {
     bool one_round;  // the one-workgroup-per-chunk one sweep runs in one round of workgroups
     bool pipe;       // one sweep by the streaming kernel over 16-bit codes, fused_chunk keys per chunk
     bool stream;     // one sweep by the streaming kernel: chunk_s[b] keys per chunk, stream_slots chunks
-    int stream_slots;
-    int32_t chunk_s[kTableBatch];
-    size_t ml_off, lse_off, otag_off, o_off, bytes;
+    int stream_slots, stream_blocks;   // chunks of all row blocks; most row blocks of a sequence
+    int32_t chunk_s[kTableBatch], blocks_s[kTableBatch], pos_s[kTableBatch];
+    size_t ml_off, lse_off, otag_off, o_off, part_off, bytes;
     SeqTable seq;
     SeqTable fseq;   // the one-sweep slots as items
 };
 
 // The streaming one sweep (verify_stream.hip) with an fp32 stash: chunks of at
 // most what half a CU's LDS holds for each sequence's rows, shortened evenly
-// when the call has fewer chunks than the device's workgroup slots.  Taken
-// instead of two sweeps for at most 40 rows and 128 chunks per unit: more rows
-// make chunks short and their waits long (48 rows over 4 x 64K keys: 330 us
-// against 275 us for two sweeps), and more chunks keep too many of the slots
-// waiting for one unit (36 rows, 228 chunks per 131K-key head: 145 against
-// 140 us), while a ragged batch of 16K-64K keys with up to 40 rows takes 292
-// us against 383 us.  False, too, where the device does not hold two
+// when the call has fewer chunks than the device's workgroup slots.  Up to 40
+// rows are one row block, taken instead of two sweeps for at most 128 chunks
+// per unit: more chunks keep too many of the slots waiting for one unit (36
+// rows, 228 chunks per 131K-key head: 145 against 140 us), while a ragged
+// batch of 16K-64K keys with up to 40 rows takes 292 us against 383 us.  More
+// rows would make chunks short and their waits long (48 rows over 4 x 64K keys
+// as one block: 330 us against 275 us for two sweeps) and run in blocks of at
+// most 32, by the rule below.  False, too, where the device does not hold two
 // workgroups per CU (or cannot be asked).
-bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, int block_pos, VerifyPlan* plan) {
-    constexpr int kTileKeys = 32, kMinTiles = 4, kSpreadTiles = 24, kMaxChunksPerUnit = 256;
-    constexpr int kStreamRows = 40, kStreamChunksPerUnit = 128;
+bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, VerifyPlan* plan) {
+    constexpr int kTileKeys = 32, kMinTiles = 4, kSpreadTiles = 24, kMaxChunksPerGroup = 256;
+    constexpr int kOneBlockRows = 40, kBlockRows = 32, kOneBlockChunks = 128;
     plan->stream = false;
     const int per_cu = stream_blocks_per_cu();
     if (per_cu < 2) return false;
     const int g = s->n_q_heads / s->n_kv_heads;
     const int64_t slots_now = (int64_t)device_cus() * per_cu;
-    const int64_t max_per_unit = std::min<int64_t>(kMaxChunksPerUnit, resident_group_cap(per_cu));
+    const int64_t resident = std::min<int64_t>(kMaxChunksPerGroup, resident_group_cap(per_cu));
     int cap[kTableBatch], cap_max = 0;
+    plan->stream_blocks = 1;
     for (int b = 0; b < s->batch; ++b) {
-        if (std::min(ql[b], block_pos) * g > kStreamRows) return false;
-        cap[b] = stream_max_tiles(std::min(ql[b], block_pos) * g);
+        if (ql[b] * g > kOneBlockRows && g > kBlockRows) return false;
+        plan->blocks_s[b] = ql[b] * g <= kOneBlockRows ? 1 : (ql[b] + kBlockRows / g - 1) / (kBlockRows / g);
+        plan->pos_s[b] = (ql[b] + plan->blocks_s[b] - 1) / plan->blocks_s[b];
+        plan->blocks_s[b] = (ql[b] + plan->pos_s[b] - 1) / plan->pos_s[b];
+        plan->stream_blocks = std::max(plan->stream_blocks, plan->blocks_s[b]);
+        cap[b] = stream_max_tiles(plan->pos_s[b] * g);
         if (cap[b] < kMinTiles) return false;
         cap_max = std::max(cap_max, cap[b]);
     }
@@ -210,7 +216,7 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, int 
         int64_t n = 0;
         for (int b = 0; b < s->batch; ++b) {
             const int keys = std::min(cap[b], limit) * kTileKeys;
-            n += (int64_t)s->n_kv_heads * ((ctx[b] + keys - 1) / keys);
+            n += (int64_t)s->n_kv_heads * plan->blocks_s[b] * ((ctx[b] + keys - 1) / keys);
         }
         return n;
     };
@@ -223,17 +229,39 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, int 
     } else {
         int max_ctx = 0;
         for (int b = 0; b < s->batch; ++b) max_ctx = std::max(max_ctx, ctx[b]);
-        const int need = (int)(((int64_t)max_ctx + kTileKeys * max_per_unit - 1) / (kTileKeys * max_per_unit));
+        const int64_t most = resident / plan->stream_blocks;
+        const int need = (int)(((int64_t)max_ctx + kTileKeys * most - 1) / (kTileKeys * most));
         limit = std::min(limit, std::max(kSpreadTiles, need));
     }
     int64_t slots = 0;
     for (int b = 0; b < s->batch; ++b) {
         plan->chunk_s[b] = std::min(cap[b], limit) * kTileKeys;
         const int64_t n = (ctx[b] + plan->chunk_s[b] - 1) / plan->chunk_s[b];
-        if (n > max_per_unit || n > kStreamChunksPerUnit) return false;
-        slots += n * s->n_kv_heads;
+        // (the blocks of a head are dispatched interleaved, so all of them
+        // have to be resident together)
+        if (n * plan->blocks_s[b] > resident || (plan->blocks_s[b] == 1 && n > kOneBlockChunks)) return false;
+        slots += n * plan->blocks_s[b] * s->n_kv_heads;
     }
+    // (a captured call takes one of the workspace's epochs per group)
+    if ((int64_t)s->batch * s->n_kv_heads * plan->stream_blocks > kEpochWords) return false;
     if (slots > (1 << 30) / kVerifyRowCap) return false;
+    if (plan->stream_blocks > 1) {
+        // Row blocks, where they are the faster of the two: a round of the
+        // streaming kernel takes about 0.045 us * (chunk + 200), one of two
+        // sweeps over 64 rows 0.034 us * (chunk + 512) for each row block.
+        // (8 KV heads; 128 rows: 8000 keys 32 against 66 us, 20K 75 / 100, 40K
+        // 138 / 219, but 4 x 32K 429 / 307; 64 rows: 20K 39 / 49, 65K 137 / 85;
+        // 48 rows: 4 x 9000 53 / 82, 2 x 65K 242 / 160.)
+        int chunk = 0, max_q = 0;
+        for (int b = 0; b < s->batch; ++b) {
+            chunk = std::max(chunk, plan->chunk_s[b]);
+            max_q = std::max(max_q, ql[b]);
+        }
+        const int n_cu = device_cus();
+        const double rounds = std::max(1.0, (double)slots / slots_now);
+        const int64_t rounds2 = ((int64_t)plan->n_items + n_cu - 1) / n_cu * ((max_q + plan->block_pos - 1) / plan->block_pos);
+        if (rounds * (chunk + 200) * 45 >= (double)rounds2 * (plan->chunk + 512) * 34) return false;
+    }
     plan->stream = true;
     plan->stream_slots = (int)slots;
     return true;
@@ -380,7 +408,7 @@ int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, con
     const size_t slots_max = (size_t)std::max(plan->n_items, plan->fused_slots);
     // per item and row: (max, sum), each word tagged in the one-sweep schedule
     plan->ml_off = kEpochBytes;
-    plan->lse_off = plan->otag_off = 0;
+    plan->lse_off = plan->otag_off = plan->part_off = 0;
     plan->o_off = plan->ml_off + align_up(slots_max * kVerifyRowCap * sizeof(uint64_t) * 2);
     plan->bytes = plan->o_off + align_up(slots_max * kVerifyRowCap * 128 * sizeof(float));
     // The streaming kernel's chunks: of 16-bit codes as planned above, else of
@@ -390,25 +418,33 @@ int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, con
     if (plan->pipe) {
         plan->stream = true;
         plan->stream_slots = plan->fused_slots;
-        for (int b = 0; b < s->batch; ++b) plan->chunk_s[b] = plan->fused_chunk;
+        plan->stream_blocks = 1;
+        for (int b = 0; b < s->batch; ++b) {
+            plan->chunk_s[b] = plan->fused_chunk;
+            plan->blocks_s[b] = 1;
+            plan->pos_s[b] = ql[b];
+        }
     } else if (!one_round) {
-        plan_stream(s, ctx, ql, plan->block_pos, plan);
+        plan_stream(s, ctx, ql, plan);
     }
     if (plan->stream) {
         int64_t rows_out = 0;
         for (int b = 0; b < s->batch; ++b)
-            rows_out += (int64_t)s->n_kv_heads * ((ctx[b] + plan->chunk_s[b] - 1) / plan->chunk_s[b]) *
-                        std::min(ql[b], plan->block_pos) * g;
+            rows_out += (int64_t)s->n_kv_heads * ((ctx[b] + plan->chunk_s[b] - 1) / plan->chunk_s[b]) * ql[b] * g;
+        const size_t groups = (size_t)s->batch * s->n_kv_heads * plan->stream_blocks;
+        const size_t score_elems = (size_t)s->batch * (p->per_head ? s->n_q_heads : s->n_kv_heads) * s->max_ctx;
         const size_t lse_off = plan->ml_off + align_up((size_t)plan->stream_slots * kVerifyRowCap * sizeof(uint64_t) * 2);
-        const size_t otag_off = lse_off + align_up((size_t)s->batch * s->n_kv_heads * kVerifyRowCap * sizeof(uint64_t));
+        const size_t otag_off = lse_off + align_up(groups * kVerifyRowCap * sizeof(uint64_t));
         const size_t o_off = otag_off + align_up((size_t)plan->stream_slots * sizeof(uint64_t));
-        const size_t bytes = o_off + align_up((size_t)rows_out * 128 * sizeof(float));
+        const size_t part_off = o_off + align_up((size_t)rows_out * 128 * sizeof(float));
+        const size_t bytes = part_off + align_up((plan->stream_blocks - 1) * score_elems * sizeof(float));
         if (bytes > bytes_limit && plan->bytes <= bytes_limit && !plan->pipe) {
             plan->stream = false;
         } else {
             plan->lse_off = lse_off;
             plan->otag_off = otag_off;
             plan->o_off = o_off;
+            plan->part_off = part_off;
             plan->bytes = std::max(plan->bytes, bytes);
         }
     }
@@ -658,38 +694,27 @@ int check_paged(const ssl_shape* s, const int32_t* ctx, const int32_t* block_tab
     return SSL_OK;
 }
 
-// The tables of block k of a streaming launch (blocks of plan.block_pos verify
-// positions, the last positions of every sequence first; a block holds only
-// the sequences that still have positions).  Returns its chunks.
-int stream_block(const ssl_shape* shape, const VerifyPlan& plan, const int32_t* ctx, const int32_t* ql, int k,
-                 StreamArgs* sa) {
+// The tables of a streaming launch.  Returns its chunks.
+int stream_tables(const ssl_shape* shape, const VerifyPlan& plan, const int32_t* ctx, const int32_t* ql, StreamArgs* sa) {
     VerifyArgs& v = sa->v;
     memset(&v.seq, 0, sizeof v.seq);
-    const int P = plan.block_pos;
-    int n = 0;
     int64_t items = 0, rows = 0;
     for (int b = 0; b < shape->batch; ++b) {
-        const int j_end = ql[b] - k * P;
-        if (j_end <= 0) continue;
-        const int j0 = std::max(0, j_end - P);
         const int64_t nchunk = (ctx[b] + plan.chunk_s[b] - 1) / plan.chunk_s[b];
-        v.seq.item_start[n] = (int32_t)items;
-        v.seq.row_start[n] = (int32_t)rows;
-        v.seq.ctx[n] = ctx[b];
-        v.seq.qlen[n] = j_end - j0;
-        v.sid[n] = b;
-        v.qoff[n] = j0;
-        v.qfull[n] = ql[b];
-        sa->chunk[n] = plan.chunk_s[b];
-        items += shape->n_kv_heads * nchunk;
-        rows += shape->n_kv_heads * nchunk * (j_end - j0) * v.group;
-        ++n;
+        v.seq.item_start[b] = (int32_t)items;
+        v.seq.row_start[b] = (int32_t)rows;
+        v.seq.ctx[b] = ctx[b];
+        v.seq.qlen[b] = ql[b];
+        sa->chunk[b] = plan.chunk_s[b];
+        sa->blocks[b] = plan.blocks_s[b];
+        sa->block_pos[b] = plan.pos_s[b];
+        items += shape->n_kv_heads * nchunk * plan.blocks_s[b];
+        rows += shape->n_kv_heads * nchunk * ql[b] * v.group;
     }
-    v.seq.n_seq = n;
-    v.seq.item_start[n] = (int32_t)items;
-    v.seq.row_start[n] = (int32_t)rows;
-    for (int i = n + 1; i <= kTableBatch; ++i) v.seq.item_start[i] = INT32_MAX;   // past every slot
-    v.score_add = k > 0 ? 1 : 0;
+    v.seq.n_seq = shape->batch;
+    v.seq.item_start[shape->batch] = (int32_t)items;
+    v.seq.row_start[shape->batch] = (int32_t)rows;
+    for (int i = shape->batch + 1; i <= kTableBatch; ++i) v.seq.item_start[i] = INT32_MAX;   // past every slot
     return (int)items;
 }
 
@@ -753,27 +778,24 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
         if (g > 16 || (g & (g - 1)) != 0) return SSL_ERR_UNSUPPORTED;
     }
     if (plan.stream) {
-        // One launch per block of positions: a launch takes its own tag, and
-        // a later block's scores are added to the earlier ones'.
+        char* ws = static_cast<char*>(workspace);
         StreamArgs sa = {};
         sa.v = a;
         sa.u16 = plan.pipe ? 1 : 0;
-        sa.lse = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + plan.lse_off);
-        sa.otag = reinterpret_cast<uint64_t*>(static_cast<char*>(workspace) + plan.otag_off);
-        rc = epochs_if_captured(stream, workspace, (int64_t)shape->batch * shape->n_kv_heads, &sa.epoch);
+        sa.lse = reinterpret_cast<uint64_t*>(ws + plan.lse_off);
+        sa.otag = reinterpret_cast<uint64_t*>(ws + plan.otag_off);
+        sa.score_part = reinterpret_cast<float*>(ws + plan.part_off);
+        sa.score_elems = (size_t)shape->batch * (params->per_head ? shape->n_q_heads : shape->n_kv_heads) * shape->max_ctx;
+        sa.max_blocks = plan.stream_blocks;
+        rc = epochs_if_captured(stream, workspace, (int64_t)shape->batch * shape->n_kv_heads * plan.stream_blocks, &sa.epoch);
         if (rc) return rc;
         rc = make_exchange(&sa.xc);
         if (rc) return rc;
+        sa.call_tag = next_call_tag();
         sa.heal = scratch && !sa.epoch ? static_cast<uint64_t*>(workspace) : nullptr;
-        int max_q = 0;
-        for (int b = 0; b < shape->batch; ++b) max_q = std::max(max_q, q_len_host[b]);
-        for (int k = 0; k * plan.block_pos < max_q; ++k) {
-            const int n_slots = stream_block(shape, plan, ctx_len_host, q_len_host, k, &sa);
-            sa.call_tag = next_call_tag();
-            sa.heal_value = mix64(sa.call_tag);
-            if (const int hip_st = hip_rc(launch_verify_stream(sa, n_slots, stream))) return hip_st;
-        }
-        return SSL_OK;
+        sa.heal_value = mix64(sa.call_tag);
+        const int n_slots = stream_tables(shape, plan, ctx_len_host, q_len_host, &sa);
+        return hip_rc(launch_verify_stream(sa, n_slots, stream));
     }
     if (use_one_sweep(plan, params)) {
         FusedArgs fa = {};

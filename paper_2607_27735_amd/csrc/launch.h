@@ -191,21 +191,29 @@ struct FusedArgs {
 };
 
 // Single-sweep verify over several rounds of workgroups, two per CU
-// (verify_stream.hip).  The items of v.seq are (unit, chunk of chunk[bt] keys)
-// slots; v.part_ml holds each unit's tagged (max, sum) words, [row][chunk] at
-// the unit's first slot * 64, and v.part_o the partial rows, each sequence's
-// from v.seq.row_start[bt] on, [KV head][chunk][row].
+// (verify_stream.hip).  The items of v.seq are the chunks of each sequence, KV
+// head by KV head, of every row block (v.sid, qoff, qfull and score_add are
+// not used).  A group is one row block of one (sequence, KV head); its slots
+// are numbered group by group.  v.part_ml holds each group's tagged (max, sum)
+// words, [row][chunk] from the group's first slot * 64 on, and v.part_o the
+// partial rows, each sequence's from v.seq.row_start on, [KV head][block]
+// [chunk][row].
 struct StreamArgs {
     VerifyArgs v;
-    uint64_t* lse;          // [units][64] tagged log-sum-exp of each row
+    uint64_t* lse;          // [groups][64] tagged log-sum-exp of each row
     uint64_t* otag;         // [slots] tags of the chunks' partial outputs
-    uint64_t* epoch;        // [units] exchange epochs (any initial value), or null
+    float* score_part;      // [max_blocks - 1][score_elems] scores of the row blocks after the first
+    size_t score_elems;     // elements of the scores tensor
+    uint64_t* epoch;        // [groups] exchange epochs (any initial value), or null
     uint64_t call_tag;      // this call's tag: unique within the process (see exchange_tag)
     Exchange xc;
-    uint64_t* heal;         // as in FusedArgs
+    uint64_t* heal;         // as in FusedArgs, by group
     uint64_t heal_value;
     int32_t u16;                  // 1: the probabilities are kept as 16-bit codes; 0: fp32
+    int32_t max_blocks;           // most row blocks of a sequence; group = unit * max_blocks + block
     int32_t chunk[kTableBatch];   // keys per chunk of each sequence, a multiple of 32
+    int32_t blocks[kTableBatch];  // row blocks of each sequence
+    int32_t block_pos[kTableBatch];   // verify positions per row block
 };
 
 // The library's static device scratch (the no-allocation entry point): its

@@ -38,10 +38,17 @@
 //      scores of its keys from the stash;
 //   5. for its share of the rows, adds the chunks' partial P.V (each chunk's
 //      landed once its own tag is there) and writes the output.
+// A KV head with more than 40 verify rows runs as several row blocks of at
+// most 32 rows, each an exchange group (a unit, in the list above) of its own;
+// the blocks of a chunk run side by side on one die and share its K and V
+// through the L2, and the blocks' scores are added by a second, small kernel.
+// (128 rows over 8 heads of 20011 keys: 98.6 us as two blocks of 64 rows of two
+// sweeps each, whose 160 items leave CUs idle; 73.7 us as four of 32 rows.)
 // Publication, tags, epochs and bounded waits are those of verify_fused.hip.
 // The waits end: workgroups are dispatched in index order, the chunks of a
-// unit are consecutive and at most half of what the device holds, publications
-// wait for nothing, and a row's reduction waits for publications only.
+// KV head, of all its row blocks, are consecutive and at most half of what the
+// device holds, publications wait for nothing, and a row's reduction waits for
+// publications only.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -69,39 +76,54 @@ constexpr size_t code_lds_bytes(int rows, int chunk) {
     return (size_t)rows * ((chunk + 8) * 2 + chunk / kTile * 4) + (size_t)std::max(kParkBytes, rows * kQStride);
 }
 
+// A chunk of one row block of one (sequence, KV head): the verify positions of
+// a sequence are cut into `blocks` row blocks, each an exchange group of its
+// own (grp) over the same chunks.
 struct SChunk {
-    int slot, unit, b, bt, c, s, slot0, nchunk, T, nq, qoff, qfull, R, key_begin, key_end, stride;
-    size_t row0;   // the unit's first row in part_o; chunk s's rows start R * s further on
+    int unit, grp, b, c, s, blk, slot0, nchunk, T, nq, qoff, qfull, R, key_begin, key_end, stride;
+    size_t row0;   // the group's first row in part_o; chunk s's rows start R * s further on
 };
 
 __device__ __forceinline__ SChunk schunk_of(const StreamArgs& fa, int slot) {
     const VerifyArgs& a = fa.v;
     // The last sequence whose items start at or before this one, sixteen scalar
     // loads together (starts past the table's end are larger than any slot).
-    int bt = 0;
+    int b = 0;
     for (int b0 = 0; b0 + 1 < a.seq.n_seq; b0 += 16) {
 #pragma unroll
-        for (int i = 1; i <= 16; ++i) bt += slot >= a.seq.item_start[b0 + i] ? 1 : 0;
+        for (int i = 1; i <= 16; ++i) b += slot >= a.seq.item_start[b0 + i] ? 1 : 0;
     }
     SChunk k;
-    const int chunk = fa.chunk[bt];
-    k.slot = slot;
-    k.bt = bt;
-    k.b = a.sid[bt];
-    k.T = a.seq.ctx[bt];
-    k.nq = a.seq.qlen[bt];
-    k.qoff = a.qoff[bt];
-    k.qfull = a.qfull[bt];
+    const int chunk = fa.chunk[b];
+    const int nb = fa.blocks[b], pos = fa.block_pos[b];
+    k.b = b;
+    k.T = a.seq.ctx[b];
+    k.qfull = a.seq.qlen[b];
     k.nchunk = (k.T + chunk - 1) / chunk;
-    const int local = slot - a.seq.item_start[bt];
-    k.c = __builtin_amdgcn_readfirstlane(local / k.nchunk);
-    k.s = local - k.c * k.nchunk;
+    const int local = slot - a.seq.item_start[b], per_head = k.nchunk * nb;
+    k.c = __builtin_amdgcn_readfirstlane(local / per_head);
+    int r = local - k.c * per_head;
+    k.blk = 0;
+    k.s = r;
+    if (nb > 1) {
+        // Eight chunks of block 0, the same eight of block 1, ...: workgroups
+        // eight apart run on one die at about the same time, so the blocks of a
+        // chunk find its K and V in that die's L2.
+        const int o = __builtin_amdgcn_readfirstlane(r / (8 * nb));
+        const int w = min(8, k.nchunk - 8 * o);
+        r -= 8 * nb * o;
+        k.blk = __builtin_amdgcn_readfirstlane(r / w);
+        k.s = 8 * o + r - k.blk * w;
+    }
+    k.qoff = k.blk * pos;
+    k.nq = min(pos, k.qfull - k.qoff);
+    k.R = k.nq * a.group;
     k.key_begin = k.s * chunk;
     k.key_end = min(k.key_begin + chunk, k.T);
-    k.unit = k.b * a.n_kv_heads + k.c;
-    k.slot0 = slot - k.s;
-    k.R = k.nq * a.group;
-    k.row0 = (size_t)a.seq.row_start[bt] + (size_t)k.c * k.nchunk * k.R;
+    k.unit = b * a.n_kv_heads + k.c;
+    k.grp = k.unit * fa.max_blocks + k.blk;
+    k.slot0 = a.seq.item_start[b] + k.c * per_head + k.blk * k.nchunk;
+    k.row0 = (size_t)a.seq.row_start[b] + (size_t)k.nchunk * a.group * (k.c * k.qfull + k.qoff);
     k.stride = fa.u16 ? chunk + 8 : max(4, chunk / kTile - 4) * kTile + 4;
     return k;
 }
@@ -221,13 +243,13 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
     const int R = k.R, stride = k.stride, g = a.group;
     using Elem = std::conditional_t<kU16, uint16_t, float>;
     Elem* stash = reinterpret_cast<Elem*>(lds);                 // [R][stride]
-    const int mts = kU16 ? fa.chunk[k.bt] / kTile : 0;
+    const int mts = kU16 ? fa.chunk[k.b] / kTile : 0;
     float* mtile = reinterpret_cast<float*>(lds + (size_t)R * stride * sizeof(Elem));   // [R][mts] references of the tiles
     char* park_c = reinterpret_cast<char*>(mtile + R * mts);    // Q during the sweep, then scratch
     float* park = reinterpret_cast<float*>(park_c);
 
     // The unit's exchange epoch, loaded first: the waits below cover it.
-    const uint64_t ep = fa.epoch ? ld_dev64(fa.epoch + k.unit) : 0ull;
+    const uint64_t ep = fa.epoch ? ld_dev64(fa.epoch + k.grp) : 0ull;
 
     // ---- 1. the sweep ---------------------------------------------------------
     u32x4 qreg[NRT];
@@ -418,9 +440,9 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
             __syncthreads();
         }
     }
-    uint64_t* lse64 = fa.lse + (size_t)k.unit * kRowCap;
+    uint64_t* lse64 = fa.lse + (size_t)k.grp * kRowCap;
     auto give_up = [&]() {
-        if (tid == 0) exchange_gave_up(fa.xc, kStatusVerify, fa.epoch ? fa.epoch + k.unit : nullptr);
+        if (tid == 0) exchange_gave_up(fa.xc, kStatusVerify, fa.epoch ? fa.epoch + k.grp : nullptr);
     };
 
     // ---- 3. the log-sum-exp of this chunk's share of the rows: s, s + nchunk, ... -----
@@ -488,7 +510,7 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
         give_up();
         return;
     }
-    if (tid == 0) st_dev64(fa.otag + k.slot, want ^ fa.xc.tag_flip);   // every wave's has landed
+    if (tid == 0) st_dev64(fa.otag + k.slot0 + k.s, want ^ fa.xc.tag_flip);   // every wave's has landed
     // a stashed probability times its factor, f[row][w] for wave w's tiles (or
     // 2^(reference of the tile - lse)), is exact
     float* f = park;   // [R][4]
@@ -543,16 +565,18 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
         }
         return G == 0 ? sc[0] : G == 1 ? sc[1] : G == 2 ? sc[2] : sc[3];
     };
+    // (a later row block's scores go to its own copy and are added afterwards)
+    float* scores = k.blk == 0 ? a.scores : fa.score_part + (size_t)(k.blk - 1) * fa.score_elems;
     auto scores_of = [&](int q4, bool valid, int tile, int w) __attribute__((always_inline)) {
         const int x = tile * kTile + 16 * ((q4 >> 2) & 1) + (q4 & 3) + 4 * G;
         auto put = [&](float* row, float v) {
-            if (valid && x < nk) row[k.key_begin + x] = a.score_add ? row[k.key_begin + x] + v : v;
+            if (valid && x < nk) row[k.key_begin + x] = v;
         };
         if (a.per_head) {   // one score row per query head of the group
             for (int hh = 0; hh < g; ++hh)
-                put(a.scores + ((size_t)k.b * a.n_q_heads + k.c * g + hh) * a.max_ctx, sum_rows(q4, tile, w, r0 + hh, g));
+                put(scores + ((size_t)k.b * a.n_q_heads + k.c * g + hh) * a.max_ctx, sum_rows(q4, tile, w, r0 + hh, g));
         } else {
-            put(a.scores + (size_t)k.unit * a.max_ctx, sum_rows(q4, tile, w, r0, 1));
+            put(scores + (size_t)k.unit * a.max_ctx, sum_rows(q4, tile, w, r0, 1));
         }
     };
     const int nq4 = max(kU16 ? ntile : ntile - kWaves, 0) * (kTile / 4);   // the tiles kept in LDS
@@ -648,8 +672,8 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
     }
     // every chunk has published, so has read the epoch
     if (tid == 0 && k.s == 0) {
-        if (fa.epoch) epoch_advance(fa.epoch + k.unit);
-        if (fa.heal) st_dev64(fa.heal + k.unit, fa.heal_value + k.unit);
+        if (fa.epoch) epoch_advance(fa.epoch + k.grp);
+        if (fa.heal) st_dev64(fa.heal + k.grp, fa.heal_value + k.grp);
     }
 }
 
@@ -671,6 +695,23 @@ __global__ __launch_bounds__(kThreads, 2) void verify_stream_kernel(StreamArgs f
 }
 
 constexpr int kStreamMaxRows = 48;
+
+// scores += the row blocks' copies, in block order (grid: key blocks, score
+// rows of `heads` per sequence).  A pass over a few MB.
+constexpr int kAddKeys = 1024;
+__global__ __launch_bounds__(kThreads) void verify_add_scores_kernel(StreamArgs fa, int heads) {
+    const int row = blockIdx.y, b = row / heads;
+    const int T = fa.v.seq.ctx[b], nb = fa.blocks[b];
+    const size_t base = (size_t)row * fa.v.max_ctx;
+#pragma unroll
+    for (int i = 0; i < kAddKeys / kThreads; ++i) {
+        const int x = blockIdx.x * kAddKeys + i * kThreads + threadIdx.x;
+        if (x >= T || nb < 2) continue;
+        float v = fa.v.scores[base + x];
+        for (int j = 0; j + 1 < nb; ++j) v += fa.score_part[(size_t)j * fa.score_elems + base + x];
+        fa.v.scores[base + x] = v;
+    }
+}
 constexpr size_t kStreamStatic = kWaves * kRowCap * sizeof(float2) + kRowCap * 4 + 16;
 constexpr size_t kStreamDynMax = 160 * 1024 / 2 - kStreamStatic;   // two workgroups per CU
 
@@ -727,10 +768,11 @@ int stream_max_code_chunk(int row_tiles) {
 
 hipError_t launch_verify_stream(const StreamArgs& a, int n_slots, hipStream_t stream) {
     size_t dyn = 0;
-    int rows = 0;
+    int rows = 0, max_ctx = 0;
     for (int b = 0; b < a.v.seq.n_seq; ++b) {
-        const int r = a.v.seq.qlen[b] * a.v.group;
+        const int r = a.block_pos[b] * a.v.group;
         rows = std::max(rows, r);
+        max_ctx = std::max(max_ctx, a.v.seq.ctx[b]);
         dyn = std::max(dyn, a.u16 ? code_lds_bytes(r, a.chunk[b]) : stream_lds_bytes(r, a.chunk[b] / kTile));
     }
     if (dyn > kStreamDynMax || rows > kStreamMaxRows) return hipErrorInvalidValue;   // (the host plans less)
@@ -747,6 +789,11 @@ hipError_t launch_verify_stream(const StreamArgs& a, int n_slots, hipStream_t st
             hipLaunchKernelGGL((verify_stream_kernel<false, true>), grid, block, dyn, stream, a);
         else
             hipLaunchKernelGGL((verify_stream_kernel<false, false>), grid, block, dyn, stream, a);
+    }
+    if (a.max_blocks > 1) {
+        const int heads = a.v.per_head ? a.v.n_q_heads : a.v.n_kv_heads;
+        hipLaunchKernelGGL(verify_add_scores_kernel, dim3((max_ctx + kAddKeys - 1) / kAddKeys, a.v.seq.n_seq * heads),
+                           block, 0, stream, a, heads);
     }
     return hipGetLastError();
 }

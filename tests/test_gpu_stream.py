@@ -64,6 +64,13 @@ CASES = {
     "fp32-rows40": (lambda: _gen(805, [44999, 300, 20001], [10, 2, 9], 16, 4), 0, False),
     # fp32, logits that rise by 120 octaves: stashed probabilities are rescaled
     "fp32-ramp40": (lambda: _ramp(_gen(806, [45056], [10], 16, 4), 120.0), 0, False),
+    # fp32 in row blocks of 32 rows: 128, 72 (a partial last block) and 16 rows (one block); more
+    # than eight chunks, not a multiple of eight
+    "fp32-blocks128": (lambda: _gen(807, [4500, 1057, 517], [16, 9, 2], 16, 2), 0, False),
+    # three blocks of four positions, the last of three; a sequence of one key
+    "fp32-blocks88": (lambda: _gen(808, [1, 2000], [1, 11], 8, 1), 0, False),
+    # a window of 16 positions: the first of three blocks has no rows in it
+    "fp32-blocks-window": (lambda: _gen(810, [2000], [40], 2, 1), 0, False),
 }
 
 
@@ -116,3 +123,34 @@ def test_stream_matches_oracle(name, per_head):
         check_score_mass(s, w)
     if "ramp" not in name:
         check_scores(s, s_ref, w.ctx_len)
+
+
+def test_row_blocks_under_capture():
+    """A captured call in row blocks: every replay, with eager calls between,
+    equals the eager call on the same inputs."""
+    w = _gen(809, [3000, 1057], [16, 9], 16, 2)
+    d = Dev(w)
+    p = B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=True)
+    assert B.verify_plan(B.verify_shape(d.q, d.k), p, w.ctx_len, w.q_len)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
+    out = torch.empty(d.q.shape, dtype=torch.float32, device="cuda")
+    sc = torch.zeros((w.batch, w.n_kv_heads, w.max_ctx), dtype=torch.float32, device="cuda")
+    cap = torch.cuda.Stream()
+    with torch.cuda.stream(cap):
+        B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, out=out, scores=sc)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=cap):
+        B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, out=out, scores=sc)
+    base = d.q.clone()
+    for r in range(4):
+        d.q.copy_(base * (1.0 - 0.125 * r))
+        out_e, sc_e = torch.empty_like(out), torch.zeros_like(sc)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, out=out_e, scores=sc_e)
+        torch.cuda.synchronize()
+        for b in range(w.batch):
+            assert torch.equal(out[b, :w.q_len[b]], out_e[b, :w.q_len[b]]), f"replay {r}"
+        assert torch.equal(sc, sc_e), f"replay {r}"
+    assert B.exchange_status() == 0
