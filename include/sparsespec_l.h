@@ -308,7 +308,8 @@ int ssl_select_workspace(const ssl_shape *shape, const ssl_params *params,
 /* The schedule ssl_select_topb would use: *one_kernel_out = 1 when the
  * partitions of every unit exchange inside one kernel (calls of at most 256
  * partitions whose units' partitions fit in half of what the device holds at
- * once), 0 for the three-kernel schedule; *part_out = positions per
+ * once), 0 otherwise (a workgroup per unit for contexts of at most 65536
+ * positions, three kernels for longer ones); *part_out = positions per
  * partition, *parts_out = partitions of the longest context.  Host only. */
 int ssl_select_plan(const ssl_shape *shape, const ssl_params *params,
                     const int32_t *ctx_len_host, int32_t *one_kernel_out, int32_t *part_out,

@@ -3,7 +3,7 @@
 // Scores are non-negative fp32, so their bit patterns order like their
 // values.  Each (sequence, KV head) unit is cut into partitions of `part`
 // positions, one 256-thread workgroup per partition, so that a handful of
-// units still spreads over the whole chip.  Two schedules:
+// units still spreads over the whole chip.  Three schedules:
 //
 // One kernel (calls of at most kSelectFuseMaxGroups partitions whose units'
 // partitions fit on the device at once, select_fused_kernel):
@@ -12,8 +12,11 @@
 // partition then resolves the exact threshold and emits its own selections
 // (see the comment above that kernel).
 //
-// Three kernels (larger calls), the kernel boundaries being the only
-// synchronisation between workgroups:
+// One workgroup per unit (larger calls of contexts of at most 65536 positions,
+// select_unit_kernel): nothing to exchange, the scores stay in the LDS.
+//
+// Three kernels (larger calls of longer contexts), the kernel boundaries being
+// the only synchronisation between workgroups:
 // hist:   each partition histograms the top 12 bits of its middle scores
 //         (2048 fine bins, plus 64 coarse bins of 32) into its own slot of
 //         the workspace: no atomics on global memory, nothing to clear.
@@ -28,6 +31,9 @@
 //         tau and the first `need` ties (lowest positions) and emits sink,
 //         middle selections (by a block scan of per-thread popcounts) and
 //         recent in ascending order.
+#include <algorithm>
+#include <atomic>
+
 #include "select_common.h"
 
 
@@ -461,6 +467,257 @@ __global__ __launch_bounds__(kSelThreads) void select_fused_kernel(SelectArgs a)
     if (done && a.epoch && tid == 0) epoch_advance(a.epoch + u);
 }
 
+// ---------------------------------------------------------------------------
+// One 1024-thread workgroup per unit: histogram of the top bits while the
+// scores go to the LDS, then each thread turns its run of 8, 16 or 32 scores
+// into two bit masks (above the threshold's bin, in it), the few in it are
+// listed in position order and resolved by two more radix passes, and each
+// thread emits its mask's bits at its place in the order.  What bounds it is
+// the VALU of one CU: 64-lane steps with a ballot, a mask and a branch per 64
+// scores took 540 cycles each, the bit masks take 100 and the histogram about
+// 200.  Contexts above 32768 positions take a second round through the LDS.
+// Against the three kernels below, in one stream of calls: 128 units of 8191
+// scores 18.8 -> 11.2 us, 32 of 24000 19.3 -> 14.0, 64 of 65536 29.5 -> 24.1,
+// 512 of 32768 79 -> 30.  With four rounds one CU is too slow (32 units of
+// 131072: 51 against 31 us), so longer contexts keep the three kernels.
+// ---------------------------------------------------------------------------
+constexpr int kUnitThreads = 1024;
+constexpr int kUnitWaves = kUnitThreads / kWave;
+constexpr int kUnitPer = 32;                              // positions per thread and round at most
+constexpr int kUnitRound = kUnitThreads * kUnitPer;
+constexpr int kUnitList = 2560;                           // candidates kept in LDS
+
+// As block_scan, over the larger workgroup.
+__device__ __forceinline__ int unit_scan(int v, int* wave_tot, int* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int incl = wave_incl_scan(v);
+    __syncthreads();
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kUnitWaves; ++w) {
+        const int t = wave_tot[w];
+        before += w < wave ? t : 0;
+        all += t;
+    }
+    *total = all;
+    return before + incl - v;
+}
+
+// Thread t holds the counts c0, c1 of the bins top, top - 1 (descending over
+// the threads): the bin where the running count reaches `remaining`, the count
+// above it and its own.  Every thread gets the result.
+__device__ __forceinline__ Digit unit_digit(int c0, int c1, int top, int remaining, int* sh, int* wave_tot) {
+    int total;
+    const int above = unit_scan(c0 + c1, wave_tot, &total);
+    if (above < remaining && remaining <= above + c0) {
+        sh[0] = top;
+        sh[1] = above;
+        sh[2] = c0;
+    } else if (above + c0 < remaining && remaining <= above + c0 + c1) {
+        sh[0] = top - 1;
+        sh[1] = above + c0;
+        sh[2] = c1;
+    }
+    __syncthreads();
+    return Digit{sh[0], sh[1], sh[2]};
+}
+
+// LDS words of a round of 1024 * per keys: one of padding after every 32, so
+// that the threads' runs of 8, 16 or 32 keys start in different banks.
+constexpr int unit_key_words(int per) { return kUnitThreads * per / 32 * 33; }
+
+template <int R>   // rounds
+__global__ __launch_bounds__(kUnitThreads) void select_unit_kernel(SelectArgs a, int per) {
+    const int u = blockIdx.x, b = u / a.n_kv_heads;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const Geom g = geom_of(a, b);
+    if (g.simple) {
+        emit_ranges<kUnitThreads>(a, u, g);
+        return;
+    }
+    extern __shared__ uint32_t keys[];   // [1024 * per], padded
+    __shared__ uint32_t hist[2][2048];   // later the two 1024-bin histograms
+    __shared__ uint32_t list[kUnitList];
+    __shared__ int wave_tot[kUnitWaves];
+    __shared__ int sh[9];
+
+    // Positions are counted from s_end.  Round r holds [r * kUnitRound, ...);
+    // thread t owns the `per` from t * per of each round.
+    const int n = g.r_start - g.s_end;
+    const float* S = a.scores + (size_t)u * a.max_ctx + g.s_end;
+    auto bits_at = [&](int x) __attribute__((always_inline)) { return __builtin_bit_cast(uint32_t, S[x]); };
+    auto key_bits = [](uint32_t v) __attribute__((always_inline)) {
+        return v == 0x80000000u ? 0u : v;   // -0 ranks as +0 (equal scores; their bins are equal, too)
+    };
+    uint32_t* my_hist = hist[lane & 1];   // (two copies: fewer lanes meet in a bin)
+    // A round of scores, coalesced, into the LDS (and the histogram).  Positions
+    // past the end are kept as copies of the last one and not counted.
+    auto stage = [&](int r, bool keep, bool count) __attribute__((always_inline)) {
+        const int x_end = min(per * kUnitThreads, n - r * kUnitRound);
+        for (int x0 = tid; x0 - tid < x_end; x0 += 8 * kUnitThreads) {
+            uint32_t* to = keys + x0 + (x0 >> 5);
+            uint32_t k[8];
+            if (x0 - tid + 8 * kUnitThreads <= x_end) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) k[i] = bits_at(r * kUnitRound + x0 + i * kUnitThreads);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (keep) to[i * (kUnitThreads / 32 * 33)] = k[i];
+                    if (count) atomicAdd(&my_hist[bin12(k[i])], 1u);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) k[i] = bits_at(min(r * kUnitRound + x0 + i * kUnitThreads, n - 1));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (keep) to[i * (kUnitThreads / 32 * 33)] = k[i];
+                    if (count && x0 + i * kUnitThreads < x_end) atomicAdd(&my_hist[bin12(k[i])], 1u);
+                }
+            }
+        }
+    };
+
+    for (int x = tid; x < 2 * 2048; x += kUnitThreads) hist[0][x] = 0u;
+    __syncthreads();
+#pragma unroll 1
+    for (int r = R - 1; r >= 0; --r) stage(r, r == 0, true);
+    __syncthreads();
+    const int top = 2047 - 2 * tid;
+    const Digit e1 = unit_digit((int)(hist[0][top] + hist[1][top]), (int)(hist[0][top - 1] + hist[1][top - 1]), top,
+                                g.take, sh, wave_tot);
+    const uint32_t d1 = (uint32_t)e1.bin;
+    int need = g.take - e1.above;
+    hist[0][tid] = 0u;   // (read before unit_digit's barriers)
+    hist[1][tid] = 0u;
+
+    // Each thread's positions above bin d1 and in it (the candidates), as bit
+    // masks, and the keys of the latter, in position order, in the list.
+    uint32_t def[R], cand[R];
+    int base[R], n_cand = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r > 0) {
+            __syncthreads();
+            stage(r, true, false);
+            __syncthreads();
+        }
+        const uint32_t* mine = keys + tid * per + (tid * per >> 5);
+        uint32_t dm = 0u, cm = 0u;
+        for (int j = per - 8; j >= 0; j -= 8) {
+#pragma unroll
+            for (int i = 7; i >= 0; --i) {
+                const uint32_t bin = bin12(mine[j + i]);
+                dm = (dm << 1) | (bin > d1 ? 1u : 0u);
+                cm = (cm << 1) | (bin == d1 ? 1u : 0u);
+            }
+        }
+        const int own = min(max(n - r * kUnitRound - tid * per, 0), per);   // positions that exist
+        const uint32_t valid = own == 32 ? ~0u : (1u << own) - 1u;
+        def[r] = dm & valid;
+        cand[r] = cm & valid;
+        int total;
+        base[r] = n_cand + unit_scan(__builtin_popcount(cand[r]), wave_tot, &total);
+        n_cand += total;
+        int x = base[r];
+        for (uint32_t m = cand[r]; m != 0u; m &= m - 1u, ++x)
+            if (x < kUnitList) list[x] = key_bits(mine[__builtin_ctz(m)]);
+    }
+    __syncthreads();
+    const bool listed = n_cand <= kUnitList;   // else the candidates are read from memory again
+    auto each_cand = [&](auto f) __attribute__((always_inline)) {   // in any order
+        if (listed) {
+            for (int x = tid; x < n_cand; x += kUnitThreads) f(list[x]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                for (uint32_t m = cand[r]; m != 0u; m &= m - 1u)
+                    f(key_bits(bits_at(r * kUnitRound + tid * per + __builtin_ctz(m))));
+        }
+    };
+    each_cand([&](uint32_t k) __attribute__((always_inline)) { atomicAdd(&hist[0][(k >> 10) & 1023u], 1u); });
+    __syncthreads();
+    const Digit e2 = unit_digit((int)hist[0][1023 - tid], 0, 1023 - tid, need, sh + 3, wave_tot);
+    need -= e2.above;
+    const uint32_t prefix = (d1 << 20) | ((uint32_t)e2.bin << 10);
+    each_cand([&](uint32_t k) __attribute__((always_inline)) {
+        if ((k & 0x7ffffc00u) == prefix) atomicAdd(&hist[1][k & 1023u], 1u);
+    });
+    __syncthreads();
+    const Digit e3 = unit_digit((int)hist[1][1023 - tid], 0, 1023 - tid, need, sh + 6, wave_tot);
+    need -= e3.above;
+    const uint32_t tau = prefix | (uint32_t)e3.bin;
+    const bool all_ties = need == e3.count;
+
+    // The candidates above tau and the first `need` equal to it, in position
+    // order, join; then everything is written in position order.
+    int32_t* out = a.idx + (size_t)u * a.budget;
+    const int end = g.s_end + g.take;   // <= budget
+    int pos = g.s_end, ties = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint32_t sel = def[r], tie = 0u;
+        int x = base[r];
+        for (uint32_t m = cand[r]; m != 0u; m &= m - 1u, ++x) {
+            const int j = __builtin_ctz(m);
+            const uint32_t k = listed ? list[x] : key_bits(bits_at(r * kUnitRound + tid * per + j));
+            if (k > tau) sel |= 1u << j;
+            if (k == tau) tie |= 1u << j;
+        }
+        if (all_ties) {
+            sel |= tie;
+        } else {
+            int total;
+            int rank = ties + unit_scan(__builtin_popcount(tie), wave_tot, &total);
+            for (uint32_t m = tie; m != 0u && rank < need; m &= m - 1u, ++rank) sel |= m & (0u - m);
+            ties += total;
+        }
+        int total;
+        int o = pos + unit_scan(__builtin_popcount(sel), wave_tot, &total);
+        for (uint32_t m = sel; m != 0u; m &= m - 1u, ++o)
+            if (o < end) out[o] = g.s_end + r * kUnitRound + tid * per + __builtin_ctz(m);
+        pos += total;
+    }
+    for (int x = tid; x < g.s_end; x += kUnitThreads) out[x] = x;
+    const int n_recent = g.T - g.r_start;
+    for (int x = tid; x < n_recent; x += kUnitThreads) out[end + x] = g.r_start + x;
+    if (u - b * a.n_kv_heads == 0 && tid == 0) a.n_idx[b] = end + n_recent;
+}
+
+// Once per device: raises the dynamic LDS limit.  False if that fails.
+bool unit_setup() {
+    constexpr int kMaxDevices = 64;
+    static std::atomic<bool> done[kMaxDevices];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const bool cached = dev >= 0 && dev < kMaxDevices;
+    if (cached && done[dev].load(std::memory_order_relaxed)) return true;
+    const int most = unit_key_words(kUnitPer) * (int)sizeof(uint32_t);
+    for (const void* f : {reinterpret_cast<const void*>(select_unit_kernel<1>),
+                          reinterpret_cast<const void*>(select_unit_kernel<2>)}) {
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+    }
+    if (cached) done[dev].store(true, std::memory_order_relaxed);
+    return true;
+}
+
+// A workgroup per unit (contexts of at most 2 * kUnitRound positions).
+void launch_unit(const SelectArgs& a, int max_t, int n_units, hipStream_t stream) {
+    const int per = max_t <= 8 * kUnitThreads ? 8 : max_t <= 16 * kUnitThreads ? 16 : kUnitPer;
+    const size_t dyn = unit_key_words(per) * sizeof(uint32_t);
+    if (max_t <= kUnitRound)
+        hipLaunchKernelGGL(select_unit_kernel<1>, dim3(n_units), dim3(kUnitThreads), dyn, stream, a, per);
+    else
+        hipLaunchKernelGGL(select_unit_kernel<2>, dim3(n_units), dim3(kUnitThreads), dyn, stream, a, per);
+}
+
 // One kernel when the caller chose it (a.fused); otherwise histogram, mark and
 // finish kernels.
 template <int NR>
@@ -510,6 +767,11 @@ int select_blocks_per_cu(int part) {
 }
 
 hipError_t launch_select(const SelectArgs& a, int n_units, hipStream_t stream) {
+    const int max_t = *std::max_element(a.ctx, a.ctx + a.batch);
+    if (!a.fused && max_t <= 2 * kUnitRound && unit_setup()) {
+        launch_unit(a, max_t, n_units, stream);
+        return hipGetLastError();
+    }
     switch (a.part / kRound) {
         case 1: launch_nr<1>(a, n_units, stream); break;
         case 2: launch_nr<2>(a, n_units, stream); break;

@@ -126,12 +126,13 @@ __device__ __forceinline__ Digit find_digit_block(const uint32_t* h, int remaini
 
 
 // Sink, then every middle position or none, then recent: ranges.
+template <int kThreads = kSelThreads>
 __device__ __forceinline__ void emit_ranges(const SelectArgs& a, int u, const Geom& g) {
     const int b = u / a.n_kv_heads;
     const int tid = threadIdx.x;
     int32_t* out = a.idx + (size_t)u * a.budget;
     const int n = g.all_mid ? g.T : g.s_end + (g.T - g.r_start);
-    for (int x = tid; x < n; x += kSelThreads)
+    for (int x = tid; x < n; x += kThreads)
         if (x < a.budget) out[x] = (g.all_mid || x < g.s_end) ? x : g.r_start + (x - g.s_end);
     if (u - b * a.n_kv_heads == 0 && tid == 0) a.n_idx[b] = n;
 }
