@@ -374,12 +374,15 @@ int ssl_select_draft(const ssl_shape *shape, const ssl_params *params,
  * step: every chunk workgroup of a
  * (sequence, KV head) is also that unit's select partition over the scores it
  * has just computed and drafts over the rows it selected, so neither the
- * scores nor the index sets are read back.  Otherwise the calls run one after
- * the other on `stream`.  ssl_decode_step_plan reports which (one_kernel_out
+ * scores nor the index sets are read back.  Otherwise verify, then select and
+ * the draft run one after the other on `stream` (for contexts of at most 32768
+ * positions as ssl_select_topb with a workgroup per unit, which exchanges
+ * nothing, and ssl_draft_attn).  ssl_decode_step_plan reports which (one_kernel_out
  * = 1 or 0).  The workspace size comes from ssl_decode_step_workspace.
  * Errors: those of the two calls.  When an exchange gives up, the status word
- * holds SSL_EXCHANGE_VERIFY or SSL_EXCHANGE_SELECT and the outputs that
- * depended on it are not written (see ssl_select_draft for the two-call form).
+ * holds SSL_EXCHANGE_VERIFY, SSL_EXCHANGE_SELECT or SSL_EXCHANGE_DRAFT and the
+ * outputs that depended on it are not written (see ssl_select_draft for the
+ * two-call form).
  */
 int ssl_decode_step_workspace(const ssl_shape *shape, const ssl_params *params,
                               const int32_t *ctx_len_host, const int32_t *q_len_host,

@@ -888,7 +888,7 @@ size_t select_draft_part_bytes(const SelectPlan& plan, int64_t units) {
 
 int select_call(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx_len_host,
                 const float* scores, int32_t* idx, int32_t* n_idx, void* workspace,
-                size_t workspace_bytes, hipStream_t stream, const DraftInputs* draft) {
+                size_t workspace_bytes, hipStream_t stream, const DraftInputs* draft, bool exchange = true) {
     int rc = check_select(shape, params, ctx_len_host);
     if (rc) return rc;
     if (!scores || !idx || !n_idx) return SSL_ERR_NULL;
@@ -897,6 +897,7 @@ int select_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
     SelectPlan plan;
     rc = plan_select(&us, ctx_len_host, &plan);
     if (rc) return rc;
+    plan.fused = plan.fused && exchange;
     const int64_t units = (int64_t)shape->batch * us.n_kv_heads;
     const size_t need = plan.bytes + (draft ? select_draft_part_bytes(plan, units) : 0);
     rc = check_workspace(workspace, workspace_bytes, need);
@@ -1139,10 +1140,20 @@ int ssl_select_draft_workspace(const ssl_shape* shape, const ssl_params* params,
     return select_draft_plan(shape, params, ctx_len_host, &plan, &fused, n_idx_host, bytes_out);
 }
 
-int ssl_select_draft(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx_len_host,
-                     const float* scores, int32_t* idx, int32_t* n_idx, const void* q_draft,
-                     const void* k_cache, const void* v_cache, void* out, void* workspace,
-                     size_t workspace_bytes, hipStream_t stream) {
+namespace {
+// step: the call is the second half of a decode step, whose scores need no
+// exchange any more.  There, select runs as one workgroup per unit and the
+// draft as its own kernel for contexts of at most kUnitStepMaxCtx positions:
+// the one-kernel form's three exchanges cost more than the second launch (2
+// units of 4096 positions, 256 entries: 17.1 -> 13.9 us; 8 of 16000, 2048
+// entries: 20.5 -> 16.5; 8 of 32768: 20.5 -> 19.2; but 8 of 60000: 25.3 ->
+// 31.3).  Their workspace must fit the one-kernel form's.
+constexpr int kUnitStepMaxCtx = 32768;
+
+int select_draft_call(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx_len_host,
+                      const float* scores, int32_t* idx, int32_t* n_idx, const void* q_draft,
+                      const void* k_cache, const void* v_cache, void* out, void* workspace,
+                      size_t workspace_bytes, hipStream_t stream, bool step) {
     SelectPlan plan;
     bool fused = false;
     int32_t n_idx_host[kTableBatch];
@@ -1155,16 +1166,33 @@ int ssl_select_draft(const ssl_shape* shape, const ssl_params* params, const int
         return SSL_ERR_ALIGN;
     rc = check_workspace(workspace, workspace_bytes, need);
     if (rc) return rc;
-    if (fused) {
+    bool exchange = true;
+    if (fused && step && *std::max_element(ctx_len_host, ctx_len_host + shape->batch) <= kUnitStepMaxCtx) {
+        const ssl_shape us = unit_shape(shape, params);
+        DraftPlan dp;
+        rc = plan_draft(&us, params, n_idx_host, &dp);
+        if (rc) return rc;
+        exchange = dp.bytes > need;
+    }
+    if (fused && exchange) {
         const DraftInputs d{q_draft, k_cache, v_cache, out};
         return select_call(shape, params, ctx_len_host, scores, idx, n_idx, workspace,
                            workspace_bytes, stream, &d);
     }
     rc = select_call(shape, params, ctx_len_host, scores, idx, n_idx, workspace, workspace_bytes,
-                     stream, nullptr);
+                     stream, nullptr, exchange);
     if (rc) return rc;
     return draft_call(shape, params, n_idx_host, q_draft, k_cache, v_cache, nullptr, 0, 0, idx, out,
                       workspace, workspace_bytes, stream);
+}
+}  // namespace
+
+int ssl_select_draft(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx_len_host,
+                     const float* scores, int32_t* idx, int32_t* n_idx, const void* q_draft,
+                     const void* k_cache, const void* v_cache, void* out, void* workspace,
+                     size_t workspace_bytes, hipStream_t stream) {
+    return select_draft_call(shape, params, ctx_len_host, scores, idx, n_idx, q_draft, k_cache, v_cache, out,
+                             workspace, workspace_bytes, stream, false);
 }
 
 }  // extern "C"
@@ -1270,8 +1298,8 @@ int ssl_decode_step(const ssl_shape* shape, const ssl_params* params, const int3
         rc = verify_call(shape, params, ctx_len_host, q_len_host, q, k_cache, v_cache, nullptr, 0, 0,
                          out, scores, workspace, workspace_bytes, stream);
         if (rc) return rc;
-        return ssl_select_draft(&ds, params, ctx_len_host, scores, idx, n_idx, q_draft, k_cache,
-                                v_cache, draft_out, workspace, workspace_bytes, stream);
+        return select_draft_call(&ds, params, ctx_len_host, scores, idx, n_idx, q_draft, k_cache,
+                                v_cache, draft_out, workspace, workspace_bytes, stream, true);
     }
     char* ws = static_cast<char*>(workspace);
     const VerifyPlan& vp = plan.v;
