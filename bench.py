@@ -59,11 +59,11 @@ REPO = os.path.dirname(os.path.abspath(__file__))
 TRAFFIC_FILE = os.path.join(REPO, "profiles", "verify_traffic_llama8b_T32K.txt")
 OUR_KERNELS = ("verify_fused_kernel", "verify_stream_kernel", "verify_stats_kernel", "verify_main_kernel",
                "verify_combine_kernel", "select_hist_kernel", "select_mark_kernel",
-               "select_finish_kernel", "select_fused_kernel", "draft_materialize_kernel",
-               "draft_kernel", "logit_stats_kernel", "spec_stats_kernel", "spec_mass_kernel",
-               "spec_sample_kernel")
+               "select_finish_kernel", "select_fused_kernel", "select_unit_kernel",
+               "verify_add_scores_kernel", "draft_materialize_kernel", "draft_kernel", "logit_stats_kernel",
+               "spec_stats_kernel", "spec_mass_kernel", "spec_sample_kernel")
 VERIFY_KERNELS = ("verify_fused_kernel", "verify_stream_kernel", "verify_stats_kernel", "verify_main_kernel",
-                  "verify_combine_kernel")
+                  "verify_combine_kernel", "verify_add_scores_kernel")
 
 
 def sources_sha256() -> str:
