@@ -478,14 +478,16 @@ __global__ __launch_bounds__(kSelThreads) void select_fused_kernel(SelectArgs a)
 // 200.  Contexts above 32768 positions take a second round through the LDS.
 // Against the three kernels below, in one stream of calls: 128 units of 8191
 // scores 18.8 -> 11.2 us, 32 of 24000 19.3 -> 14.0, 64 of 65536 29.5 -> 24.1,
-// 512 of 32768 79 -> 30.  With four rounds one CU is too slow (32 units of
+// 512 of 32768 79 -> 30 (log-normal scores, sigma 1.2; with more candidates,
+// sigma 0.15: 22.3 -> 12.7, 24.2 -> 20.8, 41.6 -> 34.7; lists over kUnitList
+// are read from memory again).  With four rounds one CU is too slow (32 units of
 // 131072: 51 against 31 us), so longer contexts keep the three kernels.
 // ---------------------------------------------------------------------------
 constexpr int kUnitThreads = 1024;
 constexpr int kUnitWaves = kUnitThreads / kWave;
 constexpr int kUnitPer = 32;                              // positions per thread and round at most
 constexpr int kUnitRound = kUnitThreads * kUnitPer;
-constexpr int kUnitList = 2560;                           // candidates kept in LDS
+constexpr int kUnitList = 4608;                           // candidates kept in LDS
 
 // As block_scan, over the larger workgroup.
 __device__ __forceinline__ int unit_scan(int v, int* wave_tot, int* total) {
@@ -538,8 +540,9 @@ __global__ __launch_bounds__(kUnitThreads) void select_unit_kernel(SelectArgs a,
         return;
     }
     extern __shared__ uint32_t keys[];   // [1024 * per], padded
-    __shared__ uint32_t hist[2][2048];   // later the two 1024-bin histograms
-    __shared__ uint32_t list[kUnitList];
+    // two 2048-bin histograms; later two of 1024 bins, then the candidates
+    __shared__ uint32_t buf[2048 + kUnitList];
+    uint32_t* const list = buf + 2048;
     __shared__ int wave_tot[kUnitWaves];
     __shared__ int sh[9];
 
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(kUnitThreads) void select_unit_kernel(SelectArgs a,
     auto key_bits = [](uint32_t v) __attribute__((always_inline)) {
         return v == 0x80000000u ? 0u : v;   // -0 ranks as +0 (equal scores; their bins are equal, too)
     };
-    uint32_t* my_hist = hist[lane & 1];   // (two copies: fewer lanes meet in a bin)
+    uint32_t* my_hist = buf + 2048 * (lane & 1);   // (two copies: fewer lanes meet in a bin)
     // A round of scores, coalesced, into the LDS (and the histogram).  Positions
     // past the end are kept as copies of the last one and not counted.
     auto stage = [&](int r, bool keep, bool count) __attribute__((always_inline)) {
@@ -579,18 +582,18 @@ __global__ __launch_bounds__(kUnitThreads) void select_unit_kernel(SelectArgs a,
         }
     };
 
-    for (int x = tid; x < 2 * 2048; x += kUnitThreads) hist[0][x] = 0u;
+    for (int x = tid; x < 2 * 2048; x += kUnitThreads) buf[x] = 0u;
     __syncthreads();
 #pragma unroll 1
     for (int r = R - 1; r >= 0; --r) stage(r, r == 0, true);
     __syncthreads();
     const int top = 2047 - 2 * tid;
-    const Digit e1 = unit_digit((int)(hist[0][top] + hist[1][top]), (int)(hist[0][top - 1] + hist[1][top - 1]), top,
+    const Digit e1 = unit_digit((int)(buf[top] + buf[2048 + top]), (int)(buf[top - 1] + buf[2047 + top]), top,
                                 g.take, sh, wave_tot);
     const uint32_t d1 = (uint32_t)e1.bin;
     int need = g.take - e1.above;
-    hist[0][tid] = 0u;   // (read before unit_digit's barriers)
-    hist[1][tid] = 0u;
+    buf[tid] = 0u;   // (read before unit_digit's barriers)
+    buf[1024 + tid] = 0u;
 
     // Each thread's positions above bin d1 and in it (the candidates), as bit
     // masks, and the keys of the latter, in position order, in the list.
@@ -636,16 +639,16 @@ __global__ __launch_bounds__(kUnitThreads) void select_unit_kernel(SelectArgs a,
                     f(key_bits(bits_at(r * kUnitRound + tid * per + __builtin_ctz(m))));
         }
     };
-    each_cand([&](uint32_t k) __attribute__((always_inline)) { atomicAdd(&hist[0][(k >> 10) & 1023u], 1u); });
+    each_cand([&](uint32_t k) __attribute__((always_inline)) { atomicAdd(&buf[(k >> 10) & 1023u], 1u); });
     __syncthreads();
-    const Digit e2 = unit_digit((int)hist[0][1023 - tid], 0, 1023 - tid, need, sh + 3, wave_tot);
+    const Digit e2 = unit_digit((int)buf[1023 - tid], 0, 1023 - tid, need, sh + 3, wave_tot);
     need -= e2.above;
     const uint32_t prefix = (d1 << 20) | ((uint32_t)e2.bin << 10);
     each_cand([&](uint32_t k) __attribute__((always_inline)) {
-        if ((k & 0x7ffffc00u) == prefix) atomicAdd(&hist[1][k & 1023u], 1u);
+        if ((k & 0x7ffffc00u) == prefix) atomicAdd(&buf[1024 + (k & 1023u)], 1u);
     });
     __syncthreads();
-    const Digit e3 = unit_digit((int)hist[1][1023 - tid], 0, 1023 - tid, need, sh + 6, wave_tot);
+    const Digit e3 = unit_digit((int)buf[2047 - tid], 0, 1023 - tid, need, sh + 6, wave_tot);
     need -= e3.above;
     const uint32_t tau = prefix | (uint32_t)e3.bin;
     const bool all_ties = need == e3.count;
