@@ -473,15 +473,13 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
         for (int o = 1; o < min(np2, kWave); o <<= 1) ml_merge(Mx, Lx, shfl_xor_f(Mx, o), shfl_xor_f(Lx, o));
         if (np2 > kWave) {   // one row over up to four waves
             float2* wpart = reinterpret_cast<float2*>(park);
-            if (lane == 0) wpart[wave] = make_float2(Mx, all_in ? Lx : -1.f);
+            if (lane == 0) wpart[wave] = make_float2(Mx, Lx);
             __syncthreads();
+            all_in = *wait_failed == 0;   // (a sum may be NaN: it says nothing about the wait)
             Mx = kEmpty;
             Lx = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                all_in = all_in && wpart[w].y >= 0.f;
-                ml_merge(Mx, Lx, wpart[w].x, wpart[w].y);
-            }
+            for (int w = 0; w < kWaves; ++w) ml_merge(Mx, Lx, wpart[w].x, wpart[w].y);
         }
         const float lse = Lx > 0.f ? Mx + fast_log2(Lx) : INFINITY;
         if (all_in && active && cc == 0) st_dev64(lse64 + row, pub | __float_as_uint(lse));

@@ -154,3 +154,50 @@ def test_row_blocks_under_capture():
             assert torch.equal(out[b, :w.q_len[b]], out_e[b, :w.q_len[b]]), f"replay {r}"
         assert torch.equal(sc, sc_e), f"replay {r}"
     assert B.exchange_status() == 0
+
+
+@pytest.mark.parametrize("name", ["codes-rows12", "fp32-rows40", "fp32-blocks128"])
+def test_a_nan_row_stays_in_its_row(name):
+    """One verify row of one head is NaN (in fp32-rows40 of a unit of more than
+    64 chunks, whose row sums several waves merge): the other rows and the other
+    KV heads' scores keep their values, no wait gives up, and a captured call
+    whose inputs are finite again is right again."""
+    make, budget, _ = CASES[name]
+    w = make()
+    d = Dev(w)
+    B.set_cu_budget(budget)
+    p = B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=True)
+    sch, chunk, items = B.verify_plan(B.verify_shape(d.q, d.k), p, w.ctx_len, w.q_len)
+    assert sch == B.VERIFY_ONE_SWEEP_PERSISTENT
+    print(f"[stream] NaN row, {name}: chunks of {chunk}, {items} items", flush=True)
+    if name == "fp32-rows40":
+        assert w.ctx_len[0] > 64 * chunk
+    out = torch.full(d.q.shape, -7.0, dtype=torch.float32, device="cuda")
+    sc = torch.full((w.batch, w.n_kv_heads, w.max_ctx), -1.0, dtype=torch.float32, device="cuda")
+    call = lambda: B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, out=out, scores=sc)
+    call()
+    torch.cuda.synchronize()
+    good = out.clone(), sc.clone()
+    row, head = (0, int(w.q_len[0]) - 1, w.group), 1   # the first query head of KV head 1
+    cap = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=cap):
+        call()
+    for run in (call, graph.replay):
+        q = d.q.clone()
+        d.q[row][:] = float("nan")
+        out.fill_(-7.0)
+        sc.fill_(-1.0)
+        torch.cuda.synchronize()
+        run()
+        torch.cuda.synchronize()
+        assert B.exchange_status() == 0
+        assert torch.isnan(out[row]).all()
+        o, s = out.clone(), sc.clone()
+        o[row] = good[0][row]
+        s[0, head] = good[1][0, head]
+        assert torch.equal(o, good[0]) and torch.equal(s, good[1])
+        d.q.copy_(q)
+        run()
+        torch.cuda.synchronize()
+        assert torch.equal(out, good[0]) and torch.equal(sc, good[1]) and B.exchange_status() == 0
