@@ -94,7 +94,9 @@ __device__ __forceinline__ void load_v(const uint16_t* vbase, int key0, int T, i
 // page.  A wave's tiles are first, first + kWaves, ...: lane l of
 // wave_pages() holds the page of the wave's tile l, loaded once before the
 // sweep, and a tile reads it back with readlane instead of waiting for a
-// table load in front of its own loads.
+// table load in front of its own loads.  A wave has 64 lanes for its pages, so
+// wave_pages() serves at most kPageRunTiles tiles.
+constexpr int kPageRunTiles = kWaves * kWave;
 __device__ __forceinline__ int wave_pages(const VerifyArgs& a, int b, int key_begin, int ntile,
                                           int first, int lane) {
     const int t = min(first + kWaves * lane, ntile - 1);

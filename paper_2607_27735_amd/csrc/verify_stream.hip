@@ -750,10 +750,12 @@ int stream_setup() {
 
 int stream_blocks_per_cu() { return stream_setup(); }
 
+// (a chunk of a paged cache has its pages in one set of wave_pages() registers;
+// the LDS alone would hold more tiles for one or two rows)
 int stream_max_tiles(int rows) {
     int tiles = 0;
     if (rows <= kStreamMaxRows)
-        while (stream_lds_bytes(rows, tiles + 1) <= kStreamDynMax) ++tiles;
+        while (tiles < kPageRunTiles && stream_lds_bytes(rows, tiles + 1) <= kStreamDynMax) ++tiles;
     return tiles;
 }
 
@@ -774,6 +776,8 @@ hipError_t launch_verify_stream(const StreamArgs& a, int n_slots, hipStream_t st
         dyn = std::max(dyn, a.u16 ? code_lds_bytes(r, a.chunk[b]) : stream_lds_bytes(r, a.chunk[b] / kTile));
     }
     if (dyn > kStreamDynMax || rows > kStreamMaxRows) return hipErrorInvalidValue;   // (the host plans less)
+    for (int b = 0; b < a.v.seq.n_seq; ++b)
+        if (a.chunk[b] > kPageRunTiles * kTile) return hipErrorInvalidValue;
     // (raises the dynamic LDS limit on the device's first launch)
     if (stream_setup() < 1) return hipErrorInvalidValue;
     const dim3 grid(n_slots), block(kThreads);

@@ -115,3 +115,40 @@ def test_paged_verify_and_draft(name, mode):
     o4 = o4.float().cpu().numpy().astype(np.float64)
     check_outputs(o4, o_ref, oa, np.ones(o_ref.shape[:2], dtype=bool), what="paged draft, wide")
     assert np.array_equal(o4, od4)
+
+
+# contexts whose chunk would hold more than 64 tiles per wave, one page register per wave and 64 tiles
+LONG_CHUNKS = {
+    # 12 KV heads of one row over 16 workgroup slots: the LDS would hold a whole context (532 tiles)
+    "streaming": (B.VERIFY_AUTO, 12, 17001, 8, B.VERIFY_ONE_SWEEP_PERSISTENT, lambda chunk: chunk <= 8192),
+}
+
+
+@pytest.mark.parametrize("name", list(LONG_CHUNKS))
+def test_paged_chunks_of_many_tiles(name):
+    mode, heads, T, cus, schedule, chunk_ok = LONG_CHUNKS[name]
+    w = generate(404, name="long-chunks", batch=1, n_q_heads=heads, n_kv_heads=heads, ctx_len=[T],
+                 q_len=[1], budget=64)
+    kp, vp, bt, max_blocks = paged(w, 32, seed=11)
+    d = Dev(w)
+    p = params_of(w, mode=mode)
+    B.set_cu_budget(cus)
+    try:
+        sch, chunk, items = B.verify_plan(B.verify_shape(d.q, d.k), p, w.ctx_len, w.q_len)
+        print(f"[paged] {name}: schedule {sch}, chunks of {chunk}, {items} items", flush=True)
+        assert sch == schedule and chunk_ok(chunk)
+        out, sc = B.verify_attn_paged(d.q, dev_bf16(kp), dev_bf16(vp), torch.from_numpy(bt).cuda(),
+                                      w.max_ctx, w.ctx_len, w.q_len, p)
+        torch.cuda.synchronize()
+        out_d, sc_d = gpu_verify(d, mode=mode)
+    finally:
+        B.set_cu_budget(0)
+    assert B.exchange_status() == 0
+    out_ref, s_ref = oracle.verify(w)
+    oabs, _ = oracle.verify(w, v=abs_v(w))
+    out, sc = out.double().cpu().numpy(), sc.double().cpu().numpy()
+    check_outputs(out, out_ref, oabs, np.ones(out.shape[:3], bool), what="paged verify O")
+    check_scores(sc, s_ref, w.ctx_len, what="paged verify S")
+    assert np.array_equal(out, out_d)
+    for b in range(w.batch):
+        assert np.array_equal(sc[b, :, :w.ctx_len[b]], sc_d[b, :, :w.ctx_len[b]])
