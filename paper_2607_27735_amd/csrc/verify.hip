@@ -76,20 +76,21 @@ __global__ __launch_bounds__(kThreads) void verify_stats_kernel(VerifyArgs a) {
     for (int rt = 0; rt < NRT; ++rt) { M[rt] = -INFINITY; L[rt] = 0.f; }
 
     const int ntile = (it.key_end - it.key_begin + kTile - 1) / kTile;
-    const int pages = kPaged ? wave_pages(a, it.b, it.key_begin, ntile, wave, lane) : 0;
-    tile_pipeline<4, KTile>(
-        wave, ntile, kWaves,
-        [&](KTile& b, int t) {
-            const int key0 = it.key_begin + t * kTile;
-            if constexpr (kPaged)
-                load_k<false>(a.k + paged_row(a, tile_page(pages, t, wave), it.c, key0) * kHeadDim,
-                              0, it.T - key0, m16, G, b.k);
-            else
-                load_k<false>(kbase, key0, it.T, m16, G, b.k);
-        },
-        [&](const KTile& b, int t) {
-            stats_tile<NRT>(a, r, b.k, it.key_begin + t * kTile, G, M, L);
-        });
+    for_page_runs<kPaged>(a, it.b, it.key_begin, ntile, wave, lane, [&](int first, int end, int pages, bool) {
+        tile_pipeline<4, KTile>(
+            first, end, kWaves,
+            [&](KTile& b, int t) {
+                const int key0 = it.key_begin + t * kTile;
+                if constexpr (kPaged)
+                    load_k<false>(a.k + paged_row(a, tile_page(pages, t, first), it.c, key0) * kHeadDim,
+                                  0, it.T - key0, m16, G, b.k);
+                else
+                    load_k<false>(kbase, key0, it.T, m16, G, b.k);
+            },
+            [&](const KTile& b, int t) {
+                stats_tile<NRT>(a, r, b.k, it.key_begin + t * kTile, G, M, L);
+            });
+    });
     // Merge the four lane groups (they saw disjoint keys of the same rows).
 #pragma unroll
     for (int rt = 0; rt < NRT; ++rt) {
@@ -214,7 +215,6 @@ __global__ __launch_bounds__(kThreads) void verify_main_kernel(VerifyArgs a) {
     float* srow = a.scores + (a.per_head ? ((size_t)it.b * a.n_q_heads + it.c * a.group) * a.max_ctx
                                          : (size_t)it.unit * a.max_ctx);
     const int ntile = (it.key_end - it.key_begin + kTile - 1) / kTile;
-    const int pages = kPaged ? wave_pages(a, it.b, it.key_begin, ntile, wave, lane) : 0;
 
     // Row log-sum-exp from the statistics of every item of this (sequence, KV
     // head), computed while the first K/V tiles are loading: thread t merges
@@ -261,17 +261,21 @@ __global__ __launch_bounds__(kThreads) void verify_main_kernel(VerifyArgs a) {
 #pragma unroll
         for (int rt = 0; rt < NRT; ++rt) oacc[jd][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    tile_pipeline<(NRT <= 2 ? 3 : 2), KVTile>(
-        wave, ntile, kWaves,
-        [&](KVTile& b, int t) {
-            load_kv_tile<kPaged, true>(a, kbase, vbase, kPaged ? tile_page(pages, t, wave) : 0, it.c,
-                                       it.key_begin + t * kTile, it.T, m16, G, b);
-        },
-        [&](const KVTile& b, int t) {
-            main_tile<NRT, kPerHead>(a, r, lse, b.k, b.v, it.key_begin + t * kTile, it.key_end, srow, m16,
-                           G, oacc);
-        },
-        row_lse);
+    for_page_runs<kPaged>(a, it.b, it.key_begin, ntile, wave, lane, [&](int first, int end, int pages, bool start) {
+        tile_pipeline<(NRT <= 2 ? 3 : 2), KVTile>(
+            first, end, kWaves,
+            [&](KVTile& b, int t) {
+                load_kv_tile<kPaged, true>(a, kbase, vbase, kPaged ? tile_page(pages, t, first) : 0, it.c,
+                                           it.key_begin + t * kTile, it.T, m16, G, b);
+            },
+            [&](const KVTile& b, int t) {
+                main_tile<NRT, kPerHead>(a, r, lse, b.k, b.v, it.key_begin + t * kTile, it.key_end, srow, m16,
+                               G, oacc);
+            },
+            [&] {
+                if (start) row_lse();   // (uniform over the workgroup)
+            });
+    });
 
     // Sum the four waves' partial outputs in LDS (fixed order), then write the
     // item's rows.  oacc[jd][rt][i] is row rt*16+m16, head-dim 32G + 8i + jd.

@@ -112,6 +112,23 @@ __device__ __forceinline__ int tile_page(int pages, int t, int first) {
     return __builtin_amdgcn_readlane(pages, (t - first) / kWaves);
 }
 
+// Calls f(first, end, pages, t0 == 0) for the wave's tiles wave, wave + kWaves,
+// ... < ntile: at once, or, with a paged cache, in runs of kPageRunTiles tiles
+// of the workgroup, each with its own page registers.
+template <bool kPaged, typename F>
+__device__ __forceinline__ void for_page_runs(const VerifyArgs& a, int b, int key_begin, int ntile, int wave,
+                                              int lane, F&& f) {
+    if constexpr (!kPaged) {
+        f(wave, ntile, 0, true);
+    } else {
+#pragma unroll 1
+        for (int t0 = 0; t0 < ntile; t0 += kPageRunTiles) {
+            const int end = min(ntile, t0 + kPageRunTiles);
+            f(t0 + wave, end, wave_pages(a, b, key_begin, end, t0 + wave, lane), t0 == 0);
+        }
+    }
+}
+
 // Loads the K and V tile at key0 from the dense cache (unit bases kbase,
 // vbase) or, with kPaged, from page `page`.
 template <bool kPaged, bool kStream, typename Tile>

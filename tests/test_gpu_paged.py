@@ -121,6 +121,8 @@ def test_paged_verify_and_draft(name, mode):
 LONG_CHUNKS = {
     # 12 KV heads of one row over 16 workgroup slots: the LDS would hold a whole context (532 tiles)
     "streaming": (B.VERIFY_AUTO, 12, 17001, 8, B.VERIFY_ONE_SWEEP_PERSISTENT, lambda chunk: chunk <= 8192),
+    # two sweeps of one item per head, 1024 tiles
+    "two-sweep": (B.VERIFY_TWO_SWEEP, 2, 32763, 2, B.VERIFY_TWO_SWEEP, lambda chunk: chunk == 32768),
 }
 
 
