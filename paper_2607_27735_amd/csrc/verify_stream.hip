@@ -695,20 +695,41 @@ __global__ __launch_bounds__(kThreads, 2) void verify_stream_kernel(StreamArgs f
 constexpr int kStreamMaxRows = 48;
 
 // scores += the row blocks' copies, in block order (grid: key blocks, score
-// rows of `heads` per sequence).  A pass over a few MB.
-constexpr int kAddKeys = 1024;
+// rows of `heads` per sequence).  A pass over a few MB, bound by its chain of
+// loads, so a thread has one key and its loads go out together.  A chunk whose
+// row blocks did not all get to their scores (a wait gave up) is left alone:
+// its copies in the workspace are not this call's.  A block got there once its
+// tag for the chunk is this call's; under capture the tag is that of the epoch
+// before the group's finisher advanced it.
 __global__ __launch_bounds__(kThreads) void verify_add_scores_kernel(StreamArgs fa, int heads) {
     const int row = blockIdx.y, b = row / heads;
-    const int T = fa.v.seq.ctx[b], nb = fa.blocks[b];
-    const size_t base = (size_t)row * fa.v.max_ctx;
+    const int T = fa.v.seq.ctx[b], nb = fa.blocks[b], chunk = fa.chunk[b];
+    const int key = blockIdx.x * kThreads + threadIdx.x;
+    if (nb < 2 || (int)blockIdx.x * kThreads >= T) return;
+    const int x = min(key, T - 1), s = x / chunk, nchunk = (T + chunk - 1) / chunk;
+    const int c = (row - b * heads) / (heads / fa.v.n_kv_heads);
+    const uint64_t* tag0 = fa.otag + fa.v.seq.item_start[b] + (size_t)c * nb * nchunk + s;
+    const uint64_t* ep0 = fa.epoch ? fa.epoch + (size_t)(b * fa.v.n_kv_heads + c) * fa.max_blocks : nullptr;
+    const size_t at = (size_t)row * fa.v.max_ctx + x;
+    float v = fa.v.scores[at];
+    bool done = key < T;
+    for (int j0 = 0; j0 < nb; j0 += 4) {
+        uint64_t tag[4], ep[4];
+        float part[4];
 #pragma unroll
-    for (int i = 0; i < kAddKeys / kThreads; ++i) {
-        const int x = blockIdx.x * kAddKeys + i * kThreads + threadIdx.x;
-        if (x >= T || nb < 2) continue;
-        float v = fa.v.scores[base + x];
-        for (int j = 0; j + 1 < nb; ++j) v += fa.score_part[(size_t)j * fa.score_elems + base + x];
-        fa.v.scores[base + x] = v;
+        for (int u = 0; u < 4; ++u) {
+            const int j = min(j0 + u, nb - 1);
+            tag[u] = tag0[(size_t)j * nchunk];
+            ep[u] = ep0 ? ep0[j] : 1ull;
+            part[u] = fa.score_part[(size_t)max(j - 1, 0) * fa.score_elems + at];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            done = done && !epoch_is_dirty(ep[u]) && tag[u] == exchange_tag(fa.call_tag, ep[u] - 1);
+            v += j0 + u > 0 && j0 + u < nb ? part[u] : 0.f;
+        }
     }
+    if (done) fa.v.scores[at] = v;
 }
 constexpr size_t kStreamStatic = kWaves * kRowCap * sizeof(float2) + kRowCap * 4 + 16;
 constexpr size_t kStreamDynMax = 160 * 1024 / 2 - kStreamStatic;   // two workgroups per CU
@@ -794,7 +815,7 @@ hipError_t launch_verify_stream(const StreamArgs& a, int n_slots, hipStream_t st
     }
     if (a.max_blocks > 1) {
         const int heads = a.v.per_head ? a.v.n_q_heads : a.v.n_kv_heads;
-        hipLaunchKernelGGL(verify_add_scores_kernel, dim3((max_ctx + kAddKeys - 1) / kAddKeys, a.v.seq.n_seq * heads),
+        hipLaunchKernelGGL(verify_add_scores_kernel, dim3((max_ctx + kThreads - 1) / kThreads, a.v.seq.n_seq * heads),
                            block, 0, stream, a, heads);
     }
     return hipGetLastError();

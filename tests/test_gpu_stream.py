@@ -201,3 +201,55 @@ def test_a_nan_row_stays_in_its_row(name):
         run()
         torch.cuda.synchronize()
         assert torch.equal(out, good[0]) and torch.equal(sc, good[1]) and B.exchange_status() == 0
+
+
+def test_row_blocks_give_up_cleanly():
+    """Row blocks whose waits all give up write neither outputs nor scores (the
+    copies of the scores in the workspace hold other data), eager and captured;
+    under capture they keep giving up until the workspace is cleared."""
+    w = _gen(811, [3000, 1057], [16, 9], 16, 2)
+    d = Dev(w)
+    p = B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=True)
+    shape = B.verify_shape(d.q, d.k)
+    assert B.verify_plan(shape, p, w.ctx_len, w.q_len)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
+    ws = torch.full((B.verify_workspace_bytes(shape, p, w.ctx_len, w.q_len),), 0x3F, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full(d.q.shape, -7.0, dtype=torch.float32, device="cuda")
+    sc = torch.full((w.batch, w.n_kv_heads, w.max_ctx), -1.0, dtype=torch.float32, device="cuda")
+    call = lambda: B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, out=out, scores=sc, workspace=ws)
+
+    def unwritten():
+        torch.cuda.synchronize()
+        return (B.exchange_status() == B.EXCHANGE_VERIFY and bool(torch.all(out == -7.0)) and
+                bool(torch.all(sc == -1.0)))
+
+    try:
+        B.test_exchange_faults(64, True)
+        call()
+        assert unwritten()
+        cap, bad, ok = torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(bad, stream=cap):
+            call()
+        B.test_exchange_faults(0, False)
+        with torch.cuda.graph(ok, stream=cap):
+            call()
+        bad.replay()
+        assert unwritten()
+        for _ in range(2):   # the clean graph finds the epochs marked
+            ok.replay()
+            assert unwritten()
+    finally:
+        B.test_exchange_faults(0, False)
+    call()                   # an eager call uses no epochs
+    torch.cuda.synchronize()
+    good = out.clone(), sc.clone()
+    out_ref, s_ref = oracle.verify(w)
+    check_scores(sc.double().cpu().numpy(), s_ref, w.ctx_len)
+    ws.fill_(0)
+    for _ in range(2):
+        out.fill_(-7.0)
+        sc.fill_(-1.0)
+        torch.cuda.synchronize()
+        ok.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, good[0]) and torch.equal(sc, good[1]) and B.exchange_status() == 0
