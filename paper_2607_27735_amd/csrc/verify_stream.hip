@@ -193,7 +193,7 @@ __device__ __forceinline__ void tile_probs(int rt, const f32x4 (&acc)[2], float 
 constexpr float kLazy = 8.f;
 template <int NRT>
 __device__ __forceinline__ void tile_probs_lazy(int rt, const f32x4 (&acc)[2], float scale, float (&M)[NRT],
-                                                float (&L)[NRT], f32x4 (&oacc)[8][NRT], f32x4 (&p)[2], float& Mr) {
+                                                float (&L)[NRT], f32x4 (&oacc)[8][NRT], f32x4 (&p)[2]) {
     float y[8];
     float mt = -INFINITY;
 #pragma unroll
@@ -211,7 +211,7 @@ __device__ __forceinline__ void tile_probs_lazy(int rt, const f32x4 (&acc)[2], f
 #pragma unroll
         for (int jd = 0; jd < 8; ++jd) oacc[jd][rt] *= alpha;
     }
-    Mr = M[rt] == kEmpty ? 0.f : M[rt];
+    const float Mr = M[rt] == kEmpty ? 0.f : M[rt];
     float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -342,14 +342,14 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
             Elem* srow = stash + (rt * 16 + m16) * stride + 4 * G;
             f32x4 (&p)[2] = plast[rt];
             if constexpr (kU16) {
-                float Mr;
-                tile_probs_lazy<NRT>(rt, acc, a.scale_log2, M, L, oacc, p, Mr);
+                tile_probs_lazy<NRT>(rt, acc, a.scale_log2, M, L, oacc, p);
                 if (own) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
                         *reinterpret_cast<uint2*>(srow + t * kTile + 16 * h) =
                             make_uint2(code_of(p[h][0]) | code_of(p[h][1]) << 16, code_of(p[h][2]) | code_of(p[h][3]) << 16);
-                    if (G == 0) mtile[(rt * 16 + m16) * mts + t] = Mr;
+                    // (kEmpty for a row that has seen no key: its factor is 0)
+                    if (G == 0) mtile[(rt * 16 + m16) * mts + t] = M[rt];
                 }
             } else {
                 tile_probs<NRT>(rt, acc, a.scale_log2, srow, t, wave, own, M, L, oacc, p);

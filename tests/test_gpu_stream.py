@@ -51,6 +51,18 @@ def _ramp(w, top):
     return w
 
 
+def _shift(w, by):
+    """Every logit moves by about `by` (log2 units): the queries of a sequence
+    get a shared part, the keys the multiple of it that gives the shift."""
+    rng = np.random.default_rng(7)
+    for b in range(w.batch):
+        a = rng.standard_normal(128)
+        q = 0.25 * bf16_bits_to_f32(w.q[b]) + a
+        k = bf16_bits_to_f32(w.k[b]) + a * (by / (w.sm_scale * 1.4427 * (a @ a)))
+        w.q[b], w.k[b] = f32_to_bf16_bits(q.astype(np.float32)), f32_to_bf16_bits(k.astype(np.float32))
+    return w
+
+
 # name: (workload, CU budget or 0, 16-bit codes?)
 CASES = {
     # one and two keys past a tile and a chunk; 12 rows; single-chunk units; T below a tile
@@ -60,6 +72,8 @@ CASES = {
     "codes-rows17": (lambda: _gen(803, [2500, 1], [17, 1], 1, 1), 4, True),
     # 33 rows, logits that rise by 120 octaves
     "codes-ramp33": (lambda: _ramp(_gen(804, [3000, 1500], [11, 5], 6, 2), 120.0), 6, True),
+    # logits near -300 (log2 units); a last chunk of two keys, none of which the first row may see
+    "codes-low": (lambda: _poison(_shift(_gen(812, [2050], [3], 8, 1), -300.0)), 5, True),
     # fp32: ragged long contexts, 40, 8 and 36 rows
     "fp32-rows40": (lambda: _gen(805, [44999, 300, 20001], [10, 2, 9], 16, 4), 0, False),
     # fp32, logits that rise by 120 octaves: stashed probabilities are rescaled
@@ -93,6 +107,8 @@ def test_stream_matches_oracle(name, per_head):
     p = B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=True, per_head=per_head)
     sch, chunk, items = B.verify_plan(B.verify_shape(d.q, d.k), p, w.ctx_len, w.q_len)
     assert sch == B.VERIFY_ONE_SWEEP_PERSISTENT, (sch, chunk, items)
+    if name == "codes-low":
+        assert w.ctx_len[0] % chunk == 2
     heads = w.n_q_heads if per_head else w.n_kv_heads
     out = torch.full(d.q.shape, -7.0, dtype=torch.float32, device="cuda")
     sc = torch.full((w.batch, heads, w.max_ctx), -1.0, dtype=torch.float32, device="cuda")
