@@ -229,7 +229,7 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, Veri
     } else {
         int max_ctx = 0;
         for (int b = 0; b < s->batch; ++b) max_ctx = std::max(max_ctx, ctx[b]);
-        const int64_t most = resident / plan->stream_blocks;
+        const int64_t most = std::max<int64_t>(1, resident / plan->stream_blocks);   // (0: refused below)
         const int need = (int)(((int64_t)max_ctx + kTileKeys * most - 1) / (kTileKeys * most));
         limit = std::min(limit, std::max(kSpreadTiles, need));
     }
