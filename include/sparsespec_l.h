@@ -239,7 +239,14 @@ int32_t ssl_index_count(int32_t T, int32_t k_sink, int32_t k_recent, int32_t bud
  * two-sweep schedule once per block of 64 / group positions, last positions
  * first, or one launch of the streaming form over blocks of at most 32 rows,
  * whichever takes fewer rounds of workgroups; the later blocks' scores are
- * added to the first's.  The workspace size covers both schedules.
+ * added to the first's.
+ * The workspace size covers every schedule and holds for these lengths only:
+ * it does not always grow with them (row blocks of the streaming form keep
+ * copies of the scores, and a longer call that takes two sweeps may need
+ * less).  A call accepts any workspace of at least the size reported for the
+ * same arguments with SSL_VERIFY_TWO_SWEEP; where the streaming form in fp32
+ * needs more than it is given, the call takes the schedule it would take
+ * without that form.
  */
 int ssl_verify_workspace(const ssl_shape *shape, const ssl_params *params,
                          const int32_t *ctx_len_host, const int32_t *q_len_host,
@@ -252,7 +259,7 @@ int ssl_verify_workspace(const ssl_shape *shape, const ssl_params *params,
  * runs on until the process ends (it fits every workspace of the five
  * workloads the library is measured on; the largest needs 105 MiB).  The call
  * itself allocates nothing.  SSL_ERR_WORKSPACE if ssl_verify_workspace reports
- * more than 128 MiB for these arguments; SSL_ERR_HIP if the array's address
+ * more than 128 MiB for these arguments with SSL_VERIFY_TWO_SWEEP; SSL_ERR_HIP if the array's address
  * cannot be found on the current device.  Every call on one GPU shares that
  * GPU's array: calls that overlap in time on one GPU (concurrent streams,
  * threads, or graphs replayed concurrently) race and give unspecified results.
@@ -265,7 +272,8 @@ int ssl_verify_attn_static(const ssl_shape *shape, const ssl_params *params,
                            const void *q, const void *k_cache, const void *v_cache,
                            void *out, float *scores, hipStream_t stream);
 
-/* The schedule ssl_verify_attn would use for these arguments: *schedule_out
+/* The schedule ssl_verify_attn would use for these arguments and a workspace
+ * of the size ssl_verify_workspace reports: *schedule_out
  * = SSL_VERIFY_ONE_SWEEP, SSL_VERIFY_ONE_SWEEP_PERSISTENT or
  * SSL_VERIFY_TWO_SWEEP, *chunk_out = keys per work item (the longest, where
  * sequences have their own), *items_out = work items (each one workgroup).

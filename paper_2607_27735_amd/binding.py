@@ -225,6 +225,19 @@ def _stream(stream) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _in_workspace(call, workspace: Optional[torch.Tensor], need: int, device, where: str) -> None:
+    """call(address, bytes) in the caller's workspace, or in a new one of
+    ``need`` bytes where there is none or the call refuses it as too small
+    (verify takes a schedule that fits where it has one that needs less)."""
+    if workspace is not None:
+        rc = call(_ptr(workspace), workspace.numel())
+        if rc != SSL_ERR_WORKSPACE or workspace.numel() >= need:
+            _check(rc, where)
+            return
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+    _check(call(_ptr(ws), ws.numel()), where)
+
+
 def _need_gpu(*ts: torch.Tensor) -> None:
     for t in ts:
         if not t.is_cuda:
@@ -303,13 +316,10 @@ def verify_attn(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, ctx_len, q_le
     if out.shape != q.shape or scores.shape != (shape.batch, heads, shape.max_ctx):
         raise ValueError("out/scores shape")
     need = verify_workspace_bytes(shape, params, ctx, ql)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
-    _check(load().ssl_verify_attn(ctypes.byref(shape), ctypes.byref(params),
-                                  ctx.ctypes.data_as(_i32p), ql.ctypes.data_as(_i32p),
-                                  _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(scores),
-                                  _ptr(workspace), workspace.numel(), _stream(stream)),
-           "ssl_verify_attn")
+    _in_workspace(lambda ws, n: load().ssl_verify_attn(
+        ctypes.byref(shape), ctypes.byref(params), ctx.ctypes.data_as(_i32p), ql.ctypes.data_as(_i32p),
+        _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(scores), ws, n, _stream(stream)),
+        workspace, need, q.device, "ssl_verify_attn")
     return out, scores
 
 
@@ -490,14 +500,10 @@ def decode_step(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, q_draft: torc
             or n_idx.shape != (shape.batch,)):
         raise ValueError("output shapes")
     need = decode_step_workspace_bytes(shape, params, ctx, ql)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
-    _check(load().ssl_decode_step(ctypes.byref(shape), ctypes.byref(params),
-                                  ctx.ctypes.data_as(_i32p), ql.ctypes.data_as(_i32p), _ptr(q),
-                                  _ptr(k), _ptr(v), _ptr(out), _ptr(scores), _ptr(idx),
-                                  _ptr(n_idx), _ptr(q_draft), _ptr(draft_out), _ptr(workspace),
-                                  workspace.numel(), _stream(stream)),
-           "ssl_decode_step")
+    _in_workspace(lambda ws, n: load().ssl_decode_step(
+        ctypes.byref(shape), ctypes.byref(params), ctx.ctypes.data_as(_i32p), ql.ctypes.data_as(_i32p),
+        _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(scores), _ptr(idx), _ptr(n_idx), _ptr(q_draft),
+        _ptr(draft_out), ws, n, _stream(stream)), workspace, need, dev, "ssl_decode_step")
     return out, scores, idx, n_idx, draft_out
 
 
@@ -575,14 +581,10 @@ def verify_attn_paged(q: torch.Tensor, k_pages: torch.Tensor, v_pages: torch.Ten
         scores = torch.zeros((batch, hq if params.per_head else hkv, max_ctx), dtype=torch.float32, device=q.device)
     _need_gpu(out, scores)
     need = verify_workspace_bytes(shape, params, ctx, ql)
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
-    _check(load().ssl_verify_attn_paged(ctypes.byref(shape), ctypes.byref(params),
-                                        ctx.ctypes.data_as(_i32p), ql.ctypes.data_as(_i32p),
-                                        _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
-                                        page, block_table.shape[1], _ptr(out), _ptr(scores),
-                                        _ptr(workspace), workspace.numel(), _stream(stream)),
-           "ssl_verify_attn_paged")
+    _in_workspace(lambda ws, n: load().ssl_verify_attn_paged(
+        ctypes.byref(shape), ctypes.byref(params), ctx.ctypes.data_as(_i32p), ql.ctypes.data_as(_i32p),
+        _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table), page, block_table.shape[1], _ptr(out),
+        _ptr(scores), ws, n, _stream(stream)), workspace, need, q.device, "ssl_verify_attn_paged")
     return out, scores
 
 

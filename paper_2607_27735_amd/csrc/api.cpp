@@ -267,8 +267,10 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, Veri
     return true;
 }
 
-// bytes_limit: the most workspace the plan may ask for where a schedule with
-// less would do (the library's own scratch).
+// bytes_limit: the workspace a call has.  The fp32 streaming form is planned
+// only where it fits: row blocks keep copies of the scores there, so a call can
+// need more than a longer one that takes two sweeps, and a workspace sized for
+// the longer one still serves it (by the schedule that needs less).
 int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql,
                 VerifyPlan* plan, size_t bytes_limit = ~(size_t)0) {
     int rc = check_shape(s);
@@ -724,7 +726,7 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
                 int32_t max_blocks, void* out, float* scores, void* workspace,
                 size_t workspace_bytes, hipStream_t stream, const StaticScratch* scratch = nullptr) {
     VerifyPlan plan;
-    int rc = plan_verify(shape, params, ctx_len_host, q_len_host, &plan, scratch ? scratch->bytes : ~(size_t)0);
+    int rc = plan_verify(shape, params, ctx_len_host, q_len_host, &plan, scratch ? scratch->bytes : workspace_bytes);
     if (rc) return rc;
     if (block_table || page_size || max_blocks) {
         rc = check_paged(shape, ctx_len_host, block_table, page_size, max_blocks);
@@ -1210,8 +1212,8 @@ struct DecodePlan {
 };
 
 int plan_decode(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql,
-                DecodePlan* plan) {
-    int rc = plan_verify(s, p, ctx, ql, &plan->v);
+                DecodePlan* plan, size_t bytes_limit = ~(size_t)0) {
+    int rc = plan_verify(s, p, ctx, ql, &plan->v, bytes_limit);
     if (rc) return rc;
     ssl_shape ds = *s;
     ds.max_q = 1;
@@ -1282,7 +1284,7 @@ int ssl_decode_step(const ssl_shape* shape, const ssl_params* params, const int3
                     const void* q_draft, void* draft_out, void* workspace, size_t workspace_bytes,
                     hipStream_t stream) {
     DecodePlan plan;
-    int rc = plan_decode(shape, params, ctx_len_host, q_len_host, &plan);
+    int rc = plan_decode(shape, params, ctx_len_host, q_len_host, &plan, workspace_bytes);
     if (rc) return rc;
     if (!q || !k_cache || !v_cache || !out || !scores || !idx || !n_idx || !q_draft || !draft_out)
         return SSL_ERR_NULL;

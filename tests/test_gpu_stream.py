@@ -269,3 +269,53 @@ def test_row_blocks_give_up_cleanly():
         ok.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, good[0]) and torch.equal(sc, good[1]) and B.exchange_status() == 0
+
+
+def test_a_smaller_workspace_takes_two_sweeps():
+    """Row blocks need more workspace than two sweeps do, also than those of a
+    longer context.  A call whose workspace holds the two sweeps only runs them,
+    also as part of a decode step; with one byte less it is refused."""
+    w = _gen(813, [3000, 1057], [16, 9], 16, 2)
+    d = Dev(w)
+    shape = B.verify_shape(d.q, d.k)
+    p2, p = (B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=True, verify_mode=m)
+             for m in (B.VERIFY_TWO_SWEEP, B.VERIFY_AUTO))
+    assert B.verify_plan(shape, p, w.ctx_len, w.q_len)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
+    calls = {
+        B.verify_workspace_bytes: lambda p, ws: B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p, workspace=ws),
+        B.decode_step_workspace_bytes: lambda p, ws: B.decode_step(d.q, d.k, d.v, d.qd, w.ctx_len, w.q_len, p,
+                                                                   workspace=ws),
+    }
+    for size, call in calls.items():
+        small = size(shape, p2, w.ctx_len, w.q_len)
+        assert size(shape, p, w.ctx_len, w.q_len) > small
+        ref = call(p2, None)
+        ws = torch.zeros(small, dtype=torch.uint8, device="cuda")
+        got = call(p, ws)
+        torch.cuda.synchronize()
+        assert ws.any()    # the call ran in it
+        assert all(torch.equal(a, b) for a, b in zip(ref, got))
+        ws.zero_()
+        call(p, ws[:-1])   # too small: the binding gives the call a workspace of its own
+        torch.cuda.synchronize()
+        assert not ws.any()
+
+
+def test_static_scratch_takes_two_sweeps_where_row_blocks_need_more():
+    """32 row blocks whose score copies exceed the library's 128 MiB: the entry
+    point without a workspace runs two sweeps, which fit."""
+    dev, g = torch.device("cuda:0"), torch.Generator(device="cuda:0")
+    g.manual_seed(814)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device=dev).to(torch.bfloat16)
+    q, k, v = rnd(8, 64, 32, 128), rnd(8, 2, 70000, 128), rnd(8, 2, 70000, 128)
+    ctx, ql = [700, 333, 64, 512, 700, 129, 600, 301], [64, 7, 64, 33, 64, 64, 1, 64]
+    p, p2 = (B.make_params(128 ** -0.5, budget=64, out_fp32=True, verify_mode=m)
+             for m in (B.VERIFY_AUTO, B.VERIFY_TWO_SWEEP))
+    shape = B.verify_shape(q, k)
+    assert B.verify_plan(shape, p, ctx, ql)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
+    assert B.verify_workspace_bytes(shape, p, ctx, ql) > (128 << 20) > B.verify_workspace_bytes(shape, p2, ctx, ql)
+    ref = B.verify_attn(q, k, v, ctx, ql, p2)
+    out, sc = torch.zeros_like(ref[0]), torch.zeros_like(ref[1])
+    B.verify_attn_static(q, k, v, ctx, ql, p, out=out, scores=sc)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref[0]) and torch.equal(sc, ref[1])
