@@ -65,7 +65,10 @@
  *    one-kernel select, draft and draft steps, logit statistics) wait for
  *    each other with bounded polls.  The plans keep every group that must be
  *    resident at once within half of what the device's CUs hold (see
- *    ssl_set_cu_budget).  A wait that still gives up (e.g. because other work
+ *    ssl_set_cu_budget), and within a quarter for the streaming verify, so
+ *    that such calls on four streams at once cannot keep each other waiting.
+ *    More exchanging calls at once, or other long kernels beside them, can:
+ *    SSL_VERIFY_TWO_SWEEP exchanges nothing inside a kernel.  A wait that still gives up (e.g. because other work
  *    held CUs) leaves that call's results unspecified and raises a bit of the
  *    device's exchange status word (ssl_exchange_status); under capture it
  *    also marks the group's epoch, and every later captured call on that

@@ -180,6 +180,16 @@ struct VerifyPlan {
     SeqTable fseq;   // the one-sweep slots as items
 };
 
+// The most chunks of the fp32 streaming form that wait for each other: 128, a
+// quarter of what the device holds at two workgroups per CU (and half of what a
+// CU budget holds).  Its calls took two sweeps, which wait for nothing, before;
+// at a quarter, the four hardware queues of a process cannot fill the device
+// with groups that wait for a workgroup still to be dispatched.
+int stream_group_max() {
+    constexpr int64_t kMaxChunksPerGroup = 128;
+    return (int)std::min(kMaxChunksPerGroup, resident_group_cap(2));
+}
+
 // The streaming one sweep (verify_stream.hip) with an fp32 stash: chunks of at
 // most what half a CU's LDS holds for each sequence's rows, shortened evenly
 // when the call has fewer chunks than the device's workgroup slots.  Up to 40
@@ -192,14 +202,14 @@ struct VerifyPlan {
 // most 32, by the rule below.  False, too, where the device does not hold two
 // workgroups per CU (or cannot be asked).
 bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, VerifyPlan* plan) {
-    constexpr int kTileKeys = 32, kMinTiles = 4, kSpreadTiles = 24, kMaxChunksPerGroup = 256;
-    constexpr int kOneBlockRows = 40, kBlockRows = 32, kOneBlockChunks = 128;
+    constexpr int kTileKeys = 32, kMinTiles = 4, kSpreadTiles = 24, kMaxChunksPerHead = 256;
+    constexpr int kOneBlockRows = 40, kBlockRows = 32;
     plan->stream = false;
     const int per_cu = stream_blocks_per_cu();
     if (per_cu < 2) return false;
     const int g = s->n_q_heads / s->n_kv_heads;
     const int64_t slots_now = (int64_t)device_cus() * per_cu;
-    const int64_t resident = std::min<int64_t>(kMaxChunksPerGroup, resident_group_cap(per_cu));
+    const int64_t per_head = std::min<int64_t>(kMaxChunksPerHead, resident_group_cap(per_cu));
     int cap[kTableBatch], cap_max = 0;
     plan->stream_blocks = 1;
     for (int b = 0; b < s->batch; ++b) {
@@ -229,7 +239,7 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, Veri
     } else {
         int max_ctx = 0;
         for (int b = 0; b < s->batch; ++b) max_ctx = std::max(max_ctx, ctx[b]);
-        const int64_t most = std::max<int64_t>(1, resident / plan->stream_blocks);   // (0: refused below)
+        const int64_t most = std::max<int64_t>(1, per_head / plan->stream_blocks);   // (0: refused below)
         const int need = (int)(((int64_t)max_ctx + kTileKeys * most - 1) / (kTileKeys * most));
         limit = std::min(limit, std::max(kSpreadTiles, need));
     }
@@ -237,9 +247,7 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, Veri
     for (int b = 0; b < s->batch; ++b) {
         plan->chunk_s[b] = std::min(cap[b], limit) * kTileKeys;
         const int64_t n = (ctx[b] + plan->chunk_s[b] - 1) / plan->chunk_s[b];
-        // (the blocks of a head are dispatched interleaved, so all of them
-        // have to be resident together)
-        if (n * plan->blocks_s[b] > resident || (plan->blocks_s[b] == 1 && n > kOneBlockChunks)) return false;
+        if (n > stream_group_max() || n * plan->blocks_s[b] > per_head) return false;
         slots += n * plan->blocks_s[b] * s->n_kv_heads;
     }
     // (a captured call takes one of the workspace's epochs per group)
@@ -789,6 +797,7 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
         sa.score_part = reinterpret_cast<float*>(ws + plan.part_off);
         sa.score_elems = (size_t)shape->batch * (params->per_head ? shape->n_q_heads : shape->n_kv_heads) * shape->max_ctx;
         sa.max_blocks = plan.stream_blocks;
+        sa.together = stream_group_max();
         rc = epochs_if_captured(stream, workspace, (int64_t)shape->batch * shape->n_kv_heads * plan.stream_blocks, &sa.epoch);
         if (rc) return rc;
         rc = make_exchange(&sa.xc);

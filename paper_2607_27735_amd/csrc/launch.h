@@ -211,6 +211,7 @@ struct StreamArgs {
     uint64_t heal_value;
     int32_t u16;                  // 1: the probabilities are kept as 16-bit codes; 0: fp32
     int32_t max_blocks;           // most row blocks of a sequence; group = unit * max_blocks + block
+    int32_t together;             // most chunks of a KV head, of all its row blocks, dispatched interleaved
     int32_t chunk[kTableBatch];   // keys per chunk of each sequence, a multiple of 32
     int32_t blocks[kTableBatch];  // row blocks of each sequence
     int32_t block_pos[kTableBatch];   // verify positions per row block

@@ -40,15 +40,17 @@
 //      landed once its own tag is there) and writes the output.
 // A KV head with more than 40 verify rows runs as several row blocks of at
 // most 32 rows, each an exchange group (a unit, in the list above) of its own;
-// the blocks of a chunk run side by side on one die and share its K and V
-// through the L2, and the blocks' scores are added by a second, small kernel.
+// the blocks of a chunk run on one die, at about the same time where the device
+// holds all of a head's, and the blocks' scores are added by a second, small
+// kernel.
 // (128 rows over 8 heads of 20011 keys: 98.6 us as two blocks of 64 rows of two
-// sweeps each, whose 160 items leave CUs idle; 73.7 us as four of 32 rows.)
+// sweeps each, whose 160 items leave CUs idle; 71.7 us as four of 32 rows.)
 // Publication, tags, epochs and bounded waits are those of verify_fused.hip.
 // The waits end: workgroups are dispatched in index order, the chunks of a
-// KV head, of all its row blocks, are consecutive and at most half of what the
-// device holds, publications wait for nothing, and a row's reduction waits for
-// publications only.
+// group (of both blocks, where two are interleaved) are consecutive and at most
+// 128, a quarter of what the device holds, so that the calls of four streams
+// cannot fill it with groups that wait; publications wait for nothing, and a
+// row's reduction waits for publications only.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -105,15 +107,24 @@ __device__ __forceinline__ SChunk schunk_of(const StreamArgs& fa, int slot) {
     int r = local - k.c * per_head;
     k.blk = 0;
     k.s = r;
-    if (nb > 1) {
-        // Eight chunks of block 0, the same eight of block 1, ...: workgroups
-        // eight apart run on one die at about the same time, so the blocks of a
-        // chunk find its K and V in that die's L2.
+    if (nb == 2 && per_head <= fa.together) {
+        // Eight chunks of block 0, the same eight of block 1: workgroups eight
+        // apart run on one die at about the same time, so the blocks of a chunk
+        // find its K and V in that die's L2 (64 rows over 2 x 20000 keys, 8
+        // heads: 76.9 us against 80.5 block after block).
         const int o = __builtin_amdgcn_readfirstlane(r / (8 * nb));
         const int w = min(8, k.nchunk - 8 * o);
         r -= 8 * nb * o;
         k.blk = __builtin_amdgcn_readfirstlane(r / w);
         k.s = 8 * o + r - k.blk * w;
+    } else if (nb > 1) {
+        // Block after block, so that only a block's own chunks have to be on the
+        // device together; each block is rotated so that (but for its last ones)
+        // a chunk runs on the die it has in block 0.  With three and more blocks
+        // a group also ends sooner (128 rows over 2 x 9000 keys, 8 heads: 69.5 us
+        // against 74.8 interleaved).
+        k.blk = __builtin_amdgcn_readfirstlane(r / k.nchunk);
+        k.s = (r - k.blk * k.nchunk + (k.blk * k.nchunk & 7)) % k.nchunk;
     }
     k.qoff = k.blk * pos;
     k.nq = min(pos, k.qfull - k.qoff);
@@ -696,7 +707,7 @@ constexpr int kStreamMaxRows = 48;
 
 // scores += the row blocks' copies, in block order (grid: key blocks, score
 // rows of `heads` per sequence).  A pass over a few MB, bound by its chain of
-// loads, so a thread has one key and its loads go out together.  A chunk whose
+// loads, so a thread has one key and the loads of two blocks go out together.  A chunk whose
 // row blocks did not all get to their scores (a wait gave up) is left alone:
 // its copies in the workspace are not this call's.  A block got there once its
 // tag for the chunk is this call's; under capture the tag is that of the epoch
@@ -713,18 +724,18 @@ __global__ __launch_bounds__(kThreads) void verify_add_scores_kernel(StreamArgs 
     const size_t at = (size_t)row * fa.v.max_ctx + x;
     float v = fa.v.scores[at];
     bool done = key < T;
-    for (int j0 = 0; j0 < nb; j0 += 4) {
-        uint64_t tag[4], ep[4];
-        float part[4];
+    for (int j0 = 0; j0 < nb; j0 += 2) {
+        uint64_t tag[2], ep[2];
+        float part[2];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 2; ++u) {
             const int j = min(j0 + u, nb - 1);
             tag[u] = tag0[(size_t)j * nchunk];
             ep[u] = ep0 ? ep0[j] : 1ull;
             part[u] = fa.score_part[(size_t)max(j - 1, 0) * fa.score_elems + at];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 2; ++u) {
             done = done && !epoch_is_dirty(ep[u]) && tag[u] == exchange_tag(fa.call_tag, ep[u] - 1);
             v += j0 + u > 0 && j0 + u < nb ? part[u] : 0.f;
         }

@@ -319,3 +319,46 @@ def test_static_scratch_takes_two_sweeps_where_row_blocks_need_more():
     B.verify_attn_static(q, k, v, ctx, ql, p, out=out, scores=sc)
     torch.cuda.synchronize()
     assert torch.equal(out, ref[0]) and torch.equal(sc, ref[1])
+
+
+def test_four_streams_at_once():
+    """Streaming calls queued on four streams together, each with a workspace of
+    its own (long groups of one block of 40 rows, two and four row blocks, more
+    workgroups in each call than the device holds): every call gives the bits it
+    gives alone and no wait gives up."""
+    dev, g = torch.device("cuda:0"), torch.Generator(device="cuda:0")
+    g.manual_seed(815)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device=dev).to(torch.bfloat16)
+    p = B.make_params(128 ** -0.5, budget=64, out_fp32=True)
+    calls = []
+    # (query heads, KV heads, contexts, positions)
+    for hq, hkv, ctx, n in [(16, 4, [60001, 44999], 10), (64, 8, [40011], 16), (32, 8, [40000], 16),
+                            (64, 8, [9000, 8003], 16)]:
+        q, k, v = rnd(len(ctx), n, hq, 128), rnd(len(ctx), hkv, max(ctx), 128), rnd(len(ctx), hkv, max(ctx), 128)
+        ql, shape = [n] * len(ctx), B.verify_shape(q, k)
+        sch, chunk, items = B.verify_plan(shape, p, ctx, ql)
+        print(f"[stream] four streams: {hq}/{hkv} heads, {ctx} keys, {n} positions: {sch}, {chunk}, {items}", flush=True)
+        assert sch == B.VERIFY_ONE_SWEEP_PERSISTENT and items > 512
+        out = torch.zeros(q.shape, dtype=torch.float32, device=dev)
+        sc = torch.zeros((len(ctx), hkv, max(ctx)), dtype=torch.float32, device=dev)
+        ws = torch.empty(B.verify_workspace_bytes(shape, p, ctx, ql), dtype=torch.uint8, device=dev)
+        st = torch.cuda.Stream()
+        call = lambda a=(q, k, v, ctx, ql, p, out, sc, ws, st): B.verify_attn(*a)
+        calls.append((call, out, sc))
+    ref = []
+    for call, out, sc in calls:
+        torch.cuda.synchronize()
+        call()
+        torch.cuda.synchronize()
+        ref.append((out.clone(), sc.clone()))
+    for _, out, sc in calls:
+        out.zero_()
+        sc.zero_()
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for call, _, _ in calls:
+            call()
+    torch.cuda.synchronize()
+    assert B.exchange_status() == 0
+    for (_, out, sc), (o, s) in zip(calls, ref):
+        assert torch.equal(out, o) and torch.equal(sc, s)
