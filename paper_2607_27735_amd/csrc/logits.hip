@@ -149,10 +149,12 @@ template <bool kF32>
 __global__ __launch_bounds__(kThreads) void logit_stats_kernel(LogitArgs a) {
     const int row = blockIdx.x / a.n_chunks, chunk = blockIdx.x - row * a.n_chunks;
     int last_row = row;   // acceptance: the sequence's row k
+    bool exchanges = a.n_chunks > 1;
     if (a.rows_per_seq > 0) {   // rows past a sequence's k + 1 are not needed
         const int b = row / a.rows_per_seq, j = row - b * a.rows_per_seq;
         if (j > a.k_len[b]) return;
         last_row = row - j + a.k_len[b];
+        exchanges = exchanges || a.k_len[b] > 0;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // The row's exchange epoch (exchange_tag), loaded before the logits so that
@@ -173,7 +175,8 @@ __global__ __launch_bounds__(kThreads) void logit_stats_kernel(LogitArgs a) {
     const size_t slot = (size_t)row * a.n_chunks;
     const uint64_t epv = scalar_here(ep), epv_last = scalar_here(ep_last);
     const uint64_t want = exchange_tag(a.call_tag, epv);
-    if (epoch_is_dirty(epv) || epoch_is_dirty(epv_last)) {   // an earlier captured call on this workspace gave up
+    if (exchanges && (epoch_is_dirty(epv) || epoch_is_dirty(epv_last))) {
+        // an earlier captured call on this workspace gave up
         if (lane == 0) exchange_gave_up(a.xc, kStatusLogits, nullptr);
         return;
     }
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(kThreads) void logit_stats_kernel(LogitArgs a) {
     const uint64_t accept_tag = exchange_tag(a.call_tag, epv_last);
     if (!row_done(a, row, st, accept_tag, a.epoch ? a.epoch + last_row : nullptr)) return;
     // every other chunk, and (the sequence's last row) every row before, has read it
-    if (lane == 0 && a.epoch && (a.n_chunks > 1 || a.rows_per_seq > 0)) epoch_advance(a.epoch + row);
+    if (lane == 0 && a.epoch && exchanges) epoch_advance(a.epoch + row);
 }
 
 }  // namespace

@@ -5,6 +5,8 @@ bit-exact.  Entropy: fp32 accumulation of e^(x - M) and x e^(x - M) over at
 most 524288 logits (32 per thread in sequence, then a merge tree) against
 fp64; the bound allowed is 2e-5 * (1 + max |x|) nats per row.  Padding
 columns past vocab hold values that would win the argmax if they were read."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -114,3 +116,37 @@ def test_greedy_accept_random_drafts():
     torch.cuda.synchronize()
     assert np.array_equal(m.cpu().numpy(), m_ref)
     assert np.array_equal(n.cpu().numpy(), n_ref)
+
+
+def test_rows_that_exchange_nothing_run_on_a_marked_workspace():
+    """Rows of one chunk (and sequences without drafted tokens) have no partner:
+    captured on a workspace whose epochs an earlier give-up marked, they are
+    right and raise no status bit."""
+    rng = np.random.default_rng(94)
+    rows, vocab = 5, 8000
+    x = _dev(_logits(rng, rows, vocab, vocab, "bf16", 2.0))
+    H_ref, a_ref = B.logit_stats(x)
+    tok = torch.zeros((rows, 1), dtype=torch.int32, device="cuda")
+    lib, k_len = B.load(), (ctypes.c_int32 * rows)()
+    ws = torch.full((1 << 15,), 0xD1A7E5C0FFEE5EED - (1 << 64), dtype=torch.int64, device="cuda")
+    H, a = torch.zeros_like(H_ref), torch.zeros_like(a_ref)
+    m, n = torch.full_like(a_ref, -1), torch.full_like(a_ref, -1)
+    x2 = torch.stack([x, torch.zeros_like(x)], dim=1).contiguous()   # [rows][max_k + 1][vocab]
+    torch.cuda.synchronize()
+    B.exchange_status()
+    graph, cap = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=cap):
+        assert lib.ssl_logit_stats(x.data_ptr(), B.SSL_DT_BF16, rows, vocab, vocab, H.data_ptr(), a.data_ptr(),
+                                   ws.data_ptr(), ws.numel() * 8, cap.cuda_stream) == 0
+        assert lib.ssl_greedy_accept(x2.data_ptr(), B.SSL_DT_BF16, rows, 1, k_len, vocab, vocab, tok.data_ptr(),
+                                     m.data_ptr(), n.data_ptr(), ws.data_ptr(), ws.numel() * 8,
+                                     cap.cuda_stream) == 0
+    for _ in range(2):
+        for t in (H, a, m, n):
+            t.fill_(-1)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(H, H_ref) and torch.equal(a, a_ref)
+        assert torch.all(m == 0) and torch.equal(n, a_ref)
+        assert B.exchange_status() == 0
