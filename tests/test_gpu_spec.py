@@ -166,3 +166,14 @@ def test_spec_accept_empirical_distribution():
     p = _probs(p_logits, 1.0)
     assert np.all(np.abs(freq - p) <= 5 * np.sqrt(p * (1 - p) / n) + 1e-3), (freq, p)
     assert stride == V
+
+
+@pytest.mark.parametrize("case", [
+    # rows of 3 chunks, 16 to a wave: 127 rows are two sets; rows of 5 chunks, 8 to a wave
+    (21, 2, 63, 20000, 20000, "bf16", 1.0, 2.0, 0.3), (22, 3, 15, 40000, 40000, "f32", 1.0, 2.0, 0.5),
+    # rows of 33 chunks, one to a wave: 41 rows are three turns of four in flight
+    (23, 1, 20, 264000, 264000, "bf16", 0.9, 2.0, 0.5),
+    # one token, two chunks
+    (24, 4, 1, 9000, 9000, "f32", 1.0, 2.0, 0.5)], ids=["3-chunks", "5-chunks", "33-chunks", "2-chunks"])
+def test_row_merges_at_their_edges(case):
+    test_spec_accept_matches_oracle(case)
