@@ -171,21 +171,20 @@ struct Weights {
     __device__ __forceinline__ void load(const SpecArgs& a, int b, int m, int chunk, int tid) {
         resid = m < a.k_len[b];
         lc::load_blocks<kF32>(row_base(a, b, m, kF32), a.vocab, chunk, tid, raw[0]);
-        lc::load_blocks<kF32>(row_base(a, b, resid ? a.max_k + 1 + m : m, kF32), a.vocab, chunk, tid, raw[1]);
+        if (resid) lc::load_blocks<kF32>(row_base(a, b, a.max_k + 1 + m, kF32), a.vocab, chunk, tid, raw[1]);
     }
     // The weights of the block at the head of the queue, the thread's load j:
     // max(0, p_m - q_m) in w and p_m in pw, or p_k in both without a residual.
     __device__ __forceinline__ void block(const SpecArgs& a, int chunk, int j, int tid, float (&w)[kPer],
                                           float (&pw)[kPer]) const {
-        float xt[kPer], xd[kPer];
-        lc::unpack_block<kF32>(raw[0][0], a.vocab, chunk, j, tid, xt);
-        lc::unpack_block<kF32>(raw[1][0], a.vocab, chunk, j, tid, xd);
+        float x[kPer];
+        lc::unpack_block<kF32>(raw[0][0], a.vocab, chunk, j, tid, x);
 #pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-            pw[e] = xt[e] == -INFINITY ? 0.f : prob(xt[e] * a.inv_tau, mt);
-            const float qd = xd[e] == -INFINITY ? 0.f : prob(xd[e] * a.inv_tau, md);
-            w[e] = resid ? fmaxf(pw[e] - qd, 0.f) : pw[e];
-        }
+        for (int e = 0; e < kPer; ++e) w[e] = pw[e] = x[e] == -INFINITY ? 0.f : prob(x[e] * a.inv_tau, mt);
+        if (!resid) return;   // (uniform)
+        lc::unpack_block<kF32>(raw[1][0], a.vocab, chunk, j, tid, x);
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) w[e] = fmaxf(pw[e] - (x[e] == -INFINITY ? 0.f : prob(x[e] * a.inv_tau, md)), 0.f);
     }
 };
 
