@@ -386,9 +386,10 @@ int ssl_select_draft(const ssl_shape *shape, const ssl_params *params,
  * (sequence, KV head) is also that unit's select partition over the scores it
  * has just computed and drafts over the rows it selected, so neither the
  * scores nor the index sets are read back.  Otherwise verify, then select and
- * the draft run one after the other on `stream` (for contexts of at most 32768
- * positions as ssl_select_topb with a workgroup per unit, which exchanges
- * nothing, and ssl_draft_attn).  ssl_decode_step_plan reports which (one_kernel_out
+ * the draft run one after the other on `stream` (as ssl_select_draft, or, for
+ * contexts of at most 16384 positions and not too many draft entries, as a
+ * select with a workgroup per unit, which exchanges nothing, and
+ * ssl_draft_attn).  ssl_decode_step_plan reports which (one_kernel_out
  * = 1 or 0).  The workspace size comes from ssl_decode_step_workspace.
  * Errors: those of the two calls.  When an exchange gives up, the status word
  * holds SSL_EXCHANGE_VERIFY, SSL_EXCHANGE_SELECT or SSL_EXCHANGE_DRAFT and the

@@ -1154,12 +1154,30 @@ int ssl_select_draft_workspace(const ssl_shape* shape, const ssl_params* params,
 namespace {
 // step: the call is the second half of a decode step, whose scores need no
 // exchange any more.  There, select runs as one workgroup per unit and the
-// draft as its own kernel for contexts of at most kUnitStepMaxCtx positions:
-// the one-kernel form's three exchanges cost more than the second launch (2
-// units of 4096 positions, 256 entries: 17.1 -> 13.9 us; 8 of 16000, 2048
-// entries: 20.5 -> 16.5; 8 of 32768: 20.5 -> 19.2; but 8 of 60000: 25.3 ->
-// 31.3).  Their workspace must fit the one-kernel form's.
-constexpr int kUnitStepMaxCtx = 32768;
+// draft as its own kernel for contexts of at most kUnitStepMaxCtx positions,
+// where the one-kernel form's three exchanges cost more than the second launch
+// (whole steps of one sequence, budget 2048: 1 to 16 units of 14000 to 16384
+// positions 1.4 to 2.6 us shorter; from 18000 to 24000 neither, of 28000 and
+// 32768 0.8 to 1.7 us longer: a workgroup's scores take it longer than a
+// sixteenth of the chip).  The one-kernel form also stays where it has half
+// the CUs and more than 256 draft entries per CU, which it drafts while its
+// selections are at hand (48 units of 4096 positions, 192 partitions: budget
+// 4096 47.2 us against 49.7, budget 1024 43.8 / 43.6; but 32 units of 3000 with
+// all positions selected, 96 partitions, 33.7 / 30.9).  The
+// other form's workspace must fit the one-kernel form's.
+constexpr int kUnitStepMaxCtx = 16384;
+
+bool step_unit_select(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx, const SelectPlan& plan,
+                      const int32_t* n_idx, size_t bytes) {
+    if (*std::max_element(ctx, ctx + shape->batch) > kUnitStepMaxCtx) return false;
+    const ssl_shape us = unit_shape(shape, params);
+    DraftPlan dp;
+    if (plan_draft(&us, params, n_idx, &dp) != SSL_OK || dp.bytes > bytes) return false;
+    int64_t entries = 0;
+    for (int b = 0; b < shape->batch; ++b) entries += (int64_t)n_idx[b] * us.n_kv_heads;
+    const int64_t slots = (int64_t)shape->batch * us.n_kv_heads * plan.parts, n_cu = device_cus();
+    return slots * 2 < n_cu || entries <= 256 * n_cu;
+}
 
 int select_draft_call(const ssl_shape* shape, const ssl_params* params, const int32_t* ctx_len_host,
                       const float* scores, int32_t* idx, int32_t* n_idx, const void* q_draft,
@@ -1177,14 +1195,7 @@ int select_draft_call(const ssl_shape* shape, const ssl_params* params, const in
         return SSL_ERR_ALIGN;
     rc = check_workspace(workspace, workspace_bytes, need);
     if (rc) return rc;
-    bool exchange = true;
-    if (fused && step && *std::max_element(ctx_len_host, ctx_len_host + shape->batch) <= kUnitStepMaxCtx) {
-        const ssl_shape us = unit_shape(shape, params);
-        DraftPlan dp;
-        rc = plan_draft(&us, params, n_idx_host, &dp);
-        if (rc) return rc;
-        exchange = dp.bytes > need;
-    }
+    const bool exchange = !(step && fused && step_unit_select(shape, params, ctx_len_host, plan, n_idx_host, need));
     if (fused && exchange) {
         const DraftInputs d{q_draft, k_cache, v_cache, out};
         return select_call(shape, params, ctx_len_host, scores, idx, n_idx, workspace,

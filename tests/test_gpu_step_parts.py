@@ -38,6 +38,36 @@ def test_step_equals_the_separate_calls(batch, hq, hkv, ctx, budget):
     assert torch.equal(dout, dout_s)   # the same kernels in the same order
 
 
+# (batch, query heads, KV heads, context, budget, positions, selected by a workgroup per unit?)
+@pytest.mark.parametrize("batch,hq,hkv,ctx,budget,ql,unit", [
+    (1, 4, 2, 16384, 512, 2, True), (1, 4, 2, 16385, 512, 2, False),    # the longest context
+    (3, 16, 16, 4096, 1365, 1, True), (3, 16, 16, 4096, 1366, 1, False),    # 256 entries per CU
+    (3, 8, 8, 4096, 4096, 1, True)])                                     # and fewer partitions than half the CUs
+def test_the_steps_select_on_both_sides_of_its_lines(batch, hq, hkv, ctx, budget, ql, unit):
+    """The step gives the bits of verify, select and draft, or of verify and
+    select_draft, whichever its rule names."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the cases lie at the lines of 256 CUs")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(ctx + budget)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, qd, k, v = (rnd(batch, ql, hq, 128), rnd(batch, hq, 128), rnd(batch, hkv, ctx, 128), rnd(batch, hkv, ctx, 128))
+    lens, qls = [ctx] * batch, [ql] * batch
+    p = B.make_params(128 ** -0.5, budget=budget, out_fp32=True, per_head=hq == hkv)   # (not the one-kernel step)
+    if hq != hkv:
+        assert not B.decode_step_plan(B.verify_shape(q, k), p, lens, qls)
+    out, scores, idx, n_idx, dout = B.decode_step(q, k, v, qd, lens, qls, p)
+    idx_u, n_u = B.select_topb(scores, lens, p, n_q_heads=hq)
+    n = [B.index_count(t, p.k_sink, p.k_recent, p.budget) for t in lens]
+    dout_u = B.draft_attn(qd, k, v, idx_u, n, p)
+    idx_x, n_x, dout_x = B.select_draft(scores, lens, p, qd, k, v)
+    torch.cuda.synchronize()
+    assert B.exchange_status() == 0
+    assert torch.equal(idx, idx_u) and torch.equal(idx, idx_x)
+    assert torch.equal(dout, dout_u if unit else dout_x)
+    assert not torch.equal(dout_u, dout_x)   # (the two merge their partial results differently)
+
+
 @pytest.mark.parametrize("vocab,k", [(17, 1), (8192, 3), (8193, 6), (128256, 5)])
 def test_greedy_acceptance_in_a_graph(vocab, k):
     batch = 3
