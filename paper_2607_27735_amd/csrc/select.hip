@@ -13,7 +13,7 @@
 // (see the comment above that kernel).
 //
 // One workgroup per unit (larger calls of contexts of at most 65536 positions,
-// select_unit_kernel): nothing to exchange, the scores stay in the LDS.
+// where that is the faster: select_unit_kernel): nothing to exchange, the scores stay in the LDS.
 //
 // Three kernels (larger calls of longer contexts), the kernel boundaries being
 // the only synchronisation between workgroups:
@@ -711,6 +711,15 @@ bool unit_setup() {
     return true;
 }
 
+// Whether a workgroup per unit is the faster of the two: its time grows with
+// the context only, that of the three kernels with the units' partitions
+// (whole steps, budget 2048, us, three kernels / a workgroup per unit: 12 units
+// of 65536 positions 114.0 / 118.1, 16 140.2 / 144.3, 24 193.3 / 193.2, 32
+// 312.5 / 306.0; 12 of 56000 107.3 / 108.9).
+bool unit_is_faster(int max_t, int n_units) {
+    return max_t <= 2 * kUnitRound && max_t <= 47000 + 1000 * n_units;
+}
+
 // A workgroup per unit (contexts of at most 2 * kUnitRound positions).
 void launch_unit(const SelectArgs& a, int max_t, int n_units, hipStream_t stream) {
     const int per = max_t <= 8 * kUnitThreads ? 8 : max_t <= 16 * kUnitThreads ? 16 : kUnitPer;
@@ -771,7 +780,7 @@ int select_blocks_per_cu(int part) {
 
 hipError_t launch_select(const SelectArgs& a, int n_units, hipStream_t stream) {
     const int max_t = *std::max_element(a.ctx, a.ctx + a.batch);
-    if (!a.fused && max_t <= 2 * kUnitRound && unit_setup()) {
+    if (!a.fused && unit_is_faster(max_t, n_units) && unit_setup()) {
         launch_unit(a, max_t, n_units, stream);
         return hipGetLastError();
     }
