@@ -732,7 +732,8 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
                 const int32_t* q_len_host, const void* q, const void* k_cache,
                 const void* v_cache, const int32_t* block_table, int32_t page_size,
                 int32_t max_blocks, void* out, float* scores, void* workspace,
-                size_t workspace_bytes, hipStream_t stream, const StaticScratch* scratch = nullptr) {
+                size_t workspace_bytes, hipStream_t stream, const StaticScratch* scratch = nullptr,
+                bool keep = false) {
     VerifyPlan plan;
     int rc = plan_verify(shape, params, ctx_len_host, q_len_host, &plan, scratch ? scratch->bytes : workspace_bytes);
     if (rc) return rc;
@@ -792,6 +793,7 @@ int verify_call(const ssl_shape* shape, const ssl_params* params, const int32_t*
         StreamArgs sa = {};
         sa.v = a;
         sa.u16 = plan.pipe ? 1 : 0;
+        sa.keep = keep ? 1 : 0;
         sa.lse = reinterpret_cast<uint64_t*>(ws + plan.lse_off);
         sa.otag = reinterpret_cast<uint64_t*>(ws + plan.otag_off);
         sa.score_part = reinterpret_cast<float*>(ws + plan.part_off);
@@ -1231,6 +1233,21 @@ struct DecodePlan {
     size_t hist_off, seg_off, tag_off, part_off, bytes;
 };
 
+// Whether verify leaves K and V in the L2 for the draft, which reads half of
+// the rows again or more, and the call is small enough for it to matter (its
+// chunks of codes run at one workgroup per CU).  K and V cold, us per step, the
+// streaming hint / without it: 40 units of 4096 positions all selected 46.4 /
+// 43.4, of 2000 with 1024 selected 48.9 / 46.1; with 1024 of 4096 41.9 / 42.2;
+// 64 units of 8191 with 4096 selected (two workgroups per CU) 94.5 / 95.1.
+bool draft_rereads(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const VerifyPlan& v) {
+    int64_t keys = 0, rows = 0;
+    for (int b = 0; b < s->batch; ++b) {
+        keys += ctx[b];
+        rows += ssl_index_count(ctx[b], p->k_sink, p->k_recent, p->budget);
+    }
+    return v.pipe && v.fused_slots <= device_cus() && 2 * rows >= keys;
+}
+
 int plan_decode(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql,
                 DecodePlan* plan, size_t bytes_limit = ~(size_t)0) {
     int rc = plan_verify(s, p, ctx, ql, &plan->v, bytes_limit);
@@ -1317,8 +1334,8 @@ int ssl_decode_step(const ssl_shape* shape, const ssl_params* params, const int3
     ssl_shape ds = *shape;
     ds.max_q = 1;
     if (!plan.one_kernel) {
-        rc = verify_call(shape, params, ctx_len_host, q_len_host, q, k_cache, v_cache, nullptr, 0, 0,
-                         out, scores, workspace, workspace_bytes, stream);
+        rc = verify_call(shape, params, ctx_len_host, q_len_host, q, k_cache, v_cache, nullptr, 0, 0, out, scores,
+                         workspace, workspace_bytes, stream, nullptr, draft_rereads(shape, params, ctx_len_host, plan.v));
         if (rc) return rc;
         return select_draft_call(&ds, params, ctx_len_host, scores, idx, n_idx, q_draft, k_cache,
                                 v_cache, draft_out, workspace, workspace_bytes, stream, true);

@@ -209,6 +209,7 @@ struct StreamArgs {
     Exchange xc;
     uint64_t* heal;         // as in FusedArgs, by group
     uint64_t heal_value;
+    int32_t keep;                 // 1 (codes, dense): K and V are loaded without the streaming hint
     int32_t u16;                  // 1: the probabilities are kept as 16-bit codes; 0: fp32
     int32_t max_blocks;           // most row blocks of a sequence; group = unit * max_blocks + block
     int32_t together;             // most chunks of a KV head, of all its row blocks, dispatched interleaved

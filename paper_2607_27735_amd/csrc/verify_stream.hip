@@ -139,9 +139,12 @@ __device__ __forceinline__ SChunk schunk_of(const StreamArgs& fa, int slot) {
     return k;
 }
 
+// (a decode step whose draft reads most of the cache again keeps it in the L2
+// instead: kKeep, see ssl_decode_step)
+template <bool kKeep>
 __device__ __forceinline__ u32x4 ld_rsrc(__amdgpu_buffer_rsrc_t r, int off) {
     constexpr int kNonTemporal = 2;   // the buffer instructions' nt bit
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kNonTemporal));
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kKeep ? 0 : kNonTemporal));
 }
 
 // The 32-key tile at key0 of a cache as a buffer of its valid rows: rows past
@@ -244,7 +247,7 @@ __device__ __forceinline__ uint32_t code_of(float v) {
 }
 __device__ __forceinline__ float of_code(uint32_t c) { return c ? __uint_as_float((c + kCodeBias) << 13) : 0.f; }
 
-template <int NRT, bool kPaged, bool kU16>
+template <int NRT, bool kPaged, bool kU16, bool kKeep>
 __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk& k, char* lds,
                                              float2* wml, float* row_lse, int* wait_failed) {
     const VerifyArgs& a = fa.v;
@@ -288,13 +291,13 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) kr[h][kb] = ld_rsrc(r, k_off + 16 * h * (kHeadDim * 2) + 64 * kb);
+            for (int kb = 0; kb < 4; ++kb) kr[h][kb] = ld_rsrc<kKeep>(r, k_off + 16 * h * (kHeadDim * 2) + 64 * kb);
     };
     auto load_v_tile = [&](int t) __attribute__((always_inline)) {
         const __amdgpu_buffer_rsrc_t r = tile_rsrc(a.v + tile_at(t), k.T - (k.key_begin + t * kTile));
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            vr[e] = ld_rsrc(r, v_off + (16 * (e >> 2) + 4 * (e & 3)) * (kHeadDim * 2));
+            vr[e] = ld_rsrc<kKeep>(r, v_off + (16 * (e >> 2) + 4 * (e & 3)) * (kHeadDim * 2));
     };
     // (in this order also after scheduling: the loop's waits count on K being
     // the older of the two)
@@ -688,7 +691,7 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
 
 // Sequences of one call have their own row counts: each workgroup runs the
 // body for its own number of row tiles (four would spill registers).
-template <bool kPaged, bool kU16>
+template <bool kPaged, bool kU16, bool kKeep = false>
 __global__ __launch_bounds__(kThreads, 2) void verify_stream_kernel(StreamArgs fa) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ float2 wml[kWaves * kRowCap];
@@ -696,11 +699,11 @@ __global__ __launch_bounds__(kThreads, 2) void verify_stream_kernel(StreamArgs f
     __shared__ int wait_failed;
     const SChunk k = schunk_of(fa, blockIdx.x);
     if (k.R <= 16)
-        stream_chunk<1, kPaged, kU16>(fa, k, lds, wml, row_lse, &wait_failed);
+        stream_chunk<1, kPaged, kU16, kKeep>(fa, k, lds, wml, row_lse, &wait_failed);
     else if (k.R <= 32)
-        stream_chunk<2, kPaged, kU16>(fa, k, lds, wml, row_lse, &wait_failed);
+        stream_chunk<2, kPaged, kU16, kKeep>(fa, k, lds, wml, row_lse, &wait_failed);
     else
-        stream_chunk<3, kPaged, kU16>(fa, k, lds, wml, row_lse, &wait_failed);
+        stream_chunk<3, kPaged, kU16, kKeep>(fa, k, lds, wml, row_lse, &wait_failed);
 }
 
 constexpr int kStreamMaxRows = 48;
@@ -759,10 +762,11 @@ int stream_setup() {
     int st = cached ? state[dev].load(std::memory_order_relaxed) : 0;
     if (st == 0) {
         int blocks = 1 << 10;
-        const void* fns[4] = {reinterpret_cast<const void*>(verify_stream_kernel<false, false>),
+        const void* fns[5] = {reinterpret_cast<const void*>(verify_stream_kernel<false, false>),
                               reinterpret_cast<const void*>(verify_stream_kernel<true, false>),
                               reinterpret_cast<const void*>(verify_stream_kernel<false, true>),
-                              reinterpret_cast<const void*>(verify_stream_kernel<true, true>)};
+                              reinterpret_cast<const void*>(verify_stream_kernel<true, true>),
+                              reinterpret_cast<const void*>(verify_stream_kernel<false, true, true>)};
         for (const void* f : fns) {
             int b = 0;
             if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStreamDynMax) != hipSuccess ||
@@ -819,7 +823,9 @@ hipError_t launch_verify_stream(const StreamArgs& a, int n_slots, hipStream_t st
         else
             hipLaunchKernelGGL((verify_stream_kernel<true, false>), grid, block, dyn, stream, a);
     } else {
-        if (a.u16)
+        if (a.u16 && a.keep)
+            hipLaunchKernelGGL((verify_stream_kernel<false, true, true>), grid, block, dyn, stream, a);
+        else if (a.u16)
             hipLaunchKernelGGL((verify_stream_kernel<false, true>), grid, block, dyn, stream, a);
         else
             hipLaunchKernelGGL((verify_stream_kernel<false, false>), grid, block, dyn, stream, a);

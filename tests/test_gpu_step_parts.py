@@ -68,6 +68,24 @@ def test_the_steps_select_on_both_sides_of_its_lines(batch, hq, hkv, ctx, budget
     assert not torch.equal(dout_u, dout_x)   # (the two merge their partial results differently)
 
 
+def test_a_step_that_drafts_over_most_rows_verifies_as_verify_attn():
+    """A small step whose draft reads half of the cache again or more loads K and
+    V without the streaming hint: the same bits as verify_attn's."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    lens, qls = [4096, 4000, 3999, 4095, 3001], [2, 1, 2, 2, 1]
+    q, qd, k, v = rnd(5, 2, 16, 128), rnd(5, 16, 128), rnd(5, 8, 4096, 128), rnd(5, 8, 4096, 128)
+    p = B.make_params(128 ** -0.5, budget=4096, out_fp32=True)
+    assert B.verify_plan(B.verify_shape(q, k), p, lens, qls)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
+    out, scores, _, _, dout = B.decode_step(q, k, v, qd, lens, qls, p)
+    out_v, scores_v = B.verify_attn(q, k, v, lens, qls, p)
+    dout_x = B.select_draft(scores_v, lens, p, qd, k, v)[2]
+    torch.cuda.synchronize()
+    assert B.exchange_status() == 0
+    assert torch.equal(out, out_v) and torch.equal(scores, scores_v) and torch.equal(dout, dout_x)
+
+
 @pytest.mark.parametrize("vocab,k", [(17, 1), (8192, 3), (8193, 6), (128256, 5)])
 def test_greedy_acceptance_in_a_graph(vocab, k):
     batch = 3
