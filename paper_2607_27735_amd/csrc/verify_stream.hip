@@ -538,63 +538,80 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
     const int r0 = max(0, k.qfull - wn - k.qoff) * g;   // first window row of this block
     const int nk = k.key_end - k.key_begin;
     // Quad q4 of the stash is four positions of a row: tile q4 / 8, wave
-    // (tile % 4), keys 16 ((q4 / 4) & 1) + (q4 & 3) + 4 i of the tile.  A wave
-    // takes 16 quads, its lane groups a quarter of the rows each (a row's quads
-    // are consecutive, so the reads are free of bank conflicts), and lane group
-    // i writes element i: two tiles' 64 scores in one store.
-    auto sum_rows = [&](int q4, int tile, int w, int first, int step) __attribute__((always_inline)) {
-        const Elem* pq = stash + 4 * q4;
-        auto get = [&](int row) __attribute__((always_inline)) {
-            if constexpr (kU16) {
-                const uint2 c = *reinterpret_cast<const uint2*>(pq + row * stride);
-                return f32x4{of_code(c.x & 0xFFFFu), of_code(c.x >> 16), of_code(c.y & 0xFFFFu), of_code(c.y >> 16)};
-            } else {
-                return *reinterpret_cast<const f32x4*>(pq + row * stride);
-            }
-        };
-        auto factor = [&](int row) __attribute__((always_inline)) {
-            if constexpr (kU16) return fast_exp2(mtile[row * mts + tile] - row_lse[row]);
-            else return f[row * kWaves + w];
-        };
+    // (tile % 4), keys 16 ((q4 / 4) & 1) + (q4 & 3) + 4 i of the tile.
+    auto get = [&](int q4, int row) __attribute__((always_inline)) {
+        const Elem* pq = stash + 4 * q4 + row * stride;
+        if constexpr (kU16) {
+            const uint2 c = *reinterpret_cast<const uint2*>(pq);
+            return f32x4{of_code(c.x & 0xFFFFu), of_code(c.x >> 16), of_code(c.y & 0xFFFFu), of_code(c.y >> 16)};
+        } else {
+            return *reinterpret_cast<const f32x4*>(pq);
+        }
+    };
+    auto factor = [&](int row, int tile, int w) __attribute__((always_inline)) {
+        if constexpr (kU16) return fast_exp2(mtile[row * mts + tile] - row_lse[row]);
+        else return f[row * kWaves + w];
+    };
+    auto key_of = [](int q4, int tile) { return tile * kTile + 16 * ((q4 >> 2) & 1) + (q4 & 3); };
+    // (a later row block's scores go to its own copy and are added afterwards)
+    float* scores = k.blk == 0 ? a.scores : fa.score_part + (size_t)(k.blk - 1) * fa.score_elems;
+    // A wave takes 16 quads, its lane groups a quarter of the rows each (a row's
+    // quads are consecutive, so the reads are free of bank conflicts), and lane
+    // group i writes element i: two tiles' 64 scores in one store.
+    auto scores_of = [&](int q4, bool valid, int tile, int w) __attribute__((always_inline)) {
         f32x4 sc = {0.f, 0.f, 0.f, 0.f};
-        int row = first + G * step;
-        for (; row + 12 * step < R; row += 16 * step) {   // four rows' reads in flight
+        int row = r0 + G;
+        for (; row + 12 < R; row += 16) {   // four rows' reads in flight
             f32x4 v[4];
             float fr[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                v[j] = get(row + 4 * j * step);
-                fr[j] = factor(row + 4 * j * step);
+                v[j] = get(q4, row + 4 * j);
+                fr[j] = factor(row + 4 * j, tile, w);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) sc += v[j] * fr[j];
         }
-        for (; row < R; row += 4 * step) sc += get(row) * factor(row);
+        for (; row < R; row += 4) sc += get(q4, row) * factor(row, tile, w);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             sc[i] += shfl_xor_f(sc[i], 16);
             sc[i] += shfl_xor_f(sc[i], 32);
         }
-        return G == 0 ? sc[0] : G == 1 ? sc[1] : G == 2 ? sc[2] : sc[3];
+        const float v = G == 0 ? sc[0] : G == 1 ? sc[1] : G == 2 ? sc[2] : sc[3];
+        const int x = key_of(q4, tile) + 4 * G;
+        if (valid && x < nk) scores[(size_t)k.unit * a.max_ctx + k.key_begin + x] = v;
     };
-    // (a later row block's scores go to its own copy and are added afterwards)
-    float* scores = k.blk == 0 ? a.scores : fa.score_part + (size_t)(k.blk - 1) * fa.score_elems;
-    auto scores_of = [&](int q4, bool valid, int tile, int w) __attribute__((always_inline)) {
-        const int x = tile * kTile + 16 * ((q4 >> 2) & 1) + (q4 & 3) + 4 * G;
-        auto put = [&](float* row, float v) {
-            if (valid && x < nk) row[k.key_begin + x] = v;
-        };
-        if (a.per_head) {   // one score row per query head of the group
-            for (int hh = 0; hh < g; ++hh)
-                put(scores + ((size_t)k.b * a.n_q_heads + k.c * g + hh) * a.max_ctx, sum_rows(q4, tile, w, r0 + hh, g));
-        } else {
-            put(scores + (size_t)k.unit * a.max_ctx, sum_rows(q4, tile, w, r0, 1));
+    // One score row per query head of the group: a head has few rows, so a
+    // thread takes a quad and a head, row after row (64 heads over 8, 29920 and
+    // 27334 keys, 2 positions: 70.6 us with the lane groups above, 53.7 so).
+    auto head_scores_of = [&](int q4, int tile, int w, int hh) __attribute__((always_inline)) {
+        f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+        int row = r0 + hh;
+        for (; row + g < R; row += 2 * g) {
+            const f32x4 v0 = get(q4, row), v1 = get(q4, row + g);
+            const float f0 = factor(row, tile, w), f1 = factor(row + g, tile, w);
+            sc += v0 * f0;
+            sc += v1 * f1;
         }
+        if (row < R) sc += get(q4, row) * factor(row, tile, w);
+        float* hrow = scores + ((size_t)k.b * a.n_q_heads + k.c * g + hh) * a.max_ctx + k.key_begin;
+        const int x = key_of(q4, tile);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (x + 4 * i < nk) hrow[x + 4 * i] = sc[i];
     };
     const int nq4 = max(kU16 ? ntile : ntile - kWaves, 0) * (kTile / 4);   // the tiles kept in LDS
-    for (int q0 = 16 * wave; q0 < nq4; q0 += 16 * kWaves) {
-        const int q4 = min(q0 + m16, nq4 - 1);
-        scores_of(q4, q0 + m16 < nq4, q4 >> 3, (q4 >> 3) & (kWaves - 1));
+    if (a.per_head) {
+        for (int it = tid; it < nq4 * g; it += kThreads) {
+            const int hh = it / nq4, q4 = it - hh * nq4;
+            head_scores_of(q4, q4 >> 3, (q4 >> 3) & (kWaves - 1), hh);
+        }
+    } else {
+        for (int q0 = 16 * wave; q0 < nq4; q0 += 16 * kWaves) {
+            const int q4 = min(q0 + m16, nq4 - 1);
+            scores_of(q4, q0 + m16 < nq4, q4 >> 3, (q4 >> 3) & (kWaves - 1));
+        }
     }
     if constexpr (!kU16) {   // the waves' last tiles, through the stash's first four tiles
         __syncthreads();
@@ -608,9 +625,14 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
             }
         }
         __syncthreads();
-        if (wave < 2) {
+        // (the tile of wave w's last 32 keys in the chunk)
+        auto last_of = [&](int w) { return w + (ntile - 1 - min(w, ntile - 1)) / kWaves * kWaves; };
+        if (a.per_head) {
+            const int q4 = tid & 31, w = q4 >> 3;
+            for (int hh = tid >> 5; w < ntile && hh < g; hh += kThreads / 32) head_scores_of(q4, last_of(w), w, hh);
+        } else if (wave < 2) {
             const int q4 = 16 * wave + m16, w = q4 >> 3;
-            scores_of(q4, w < ntile, w + (ntile - 1 - min(w, ntile - 1)) / kWaves * kWaves, w);
+            scores_of(q4, w < ntile, last_of(w), w);
         }
     }
 
