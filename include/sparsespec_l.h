@@ -241,8 +241,8 @@ int32_t ssl_index_count(int32_t T, int32_t k_sink, int32_t k_recent, int32_t bud
  * the last W = 16 prompt positions of a group of 8), the call runs either the
  * two-sweep schedule once per block of 64 / group positions, last positions
  * first, or one launch of the streaming form over blocks of at most 32 rows,
- * whichever takes fewer rounds of workgroups; the later blocks' scores are
- * added to the first's.
+ * whichever is expected to be faster; the later blocks' scores are added to
+ * the first's.
  * The workspace size covers every schedule and holds for these lengths only:
  * it does not always grow with them (row blocks of the streaming form keep
  * copies of the scores, and a longer call that takes two sweeps may need

@@ -180,6 +180,18 @@ struct VerifyPlan {
     SeqTable fseq;   // the one-sweep slots as items
 };
 
+// Whether the one-workgroup-per-chunk one sweep is taken rather than two
+// sweeps.  AUTO takes it where it fits and a KV head has at most 32 verify rows,
+// or more when it runs in one round of workgroups; over several rounds at 33-64
+// rows (one wave per SIMD, logits of every row in LDS) it waits across rounds
+// and two sweeps are faster (70B shape: 457 vs 336 us), while in one round it
+// wins (44 rows at 16K: 26.1 vs 36.5 us; 48 rows at 8K: 21.8 vs 29.6 us; 64 rows
+// at 8K: 25.2 vs 34.0 us).
+bool one_sweep_wins(const VerifyPlan& plan, const ssl_params* p) {
+    if (!plan.fused_ok || p->verify_mode == SSL_VERIFY_TWO_SWEEP) return false;
+    return p->verify_mode == SSL_VERIFY_ONE_SWEEP || plan.row_tiles <= 2 || plan.one_round;
+}
+
 // The most chunks of the fp32 streaming form that wait for each other: 128, a
 // quarter of what the device holds at two workgroups per CU (and half of what a
 // CU budget holds).  Its calls took two sweeps, which wait for nothing, before;
@@ -190,18 +202,51 @@ int stream_group_max() {
     return (int)std::min(kMaxChunksPerGroup, resident_group_cap(2));
 }
 
+// Whether the planned chunks (slots of them) are expected to take less than two
+// sweeps.  Both times in ns, fitted to 6000 calls of random shapes (1 to 128
+// rows, 600 to 131000 keys, K and V cold; median error 5%, 12% at the ninth
+// decile): a round of two workgroups per CU against rounds of items, whose row
+// tiles cost as much as their keys, and the score rows of every query head
+// where each has its own.  The streaming one's has 8% on top, or 12% up to two
+// blocks, where the two are often close: of 7900 calls 25 then take up to 1.14
+// times as long as two sweeps would and 70 up to 1.39 times as long as the
+// streaming form (without the rule 450, up to 1.56 times).  (us, stream / two:
+// 3 x 9246 keys, 56 rows, 8 heads, per head 71 / 61; 2 x 42384, 48 rows 151 /
+// 126; 3 x 35528-48916, 40 rows 149 / 132; but 20011 keys, 128 rows 71 / 99; 4 x
+// 9000, 48 rows 53 / 82; 58446, 36 rows 74 / 73.)
+bool stream_beats_two_sweeps(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql,
+                             const VerifyPlan& plan, int64_t slots, int64_t slots_now) {
+    int chunk = 0, max_q = 0, blocks = 0;
+    double keys = 0.;
+    for (int b = 0; b < s->batch; ++b) {
+        chunk = std::max(chunk, plan.chunk_s[b]);
+        max_q = std::max(max_q, ql[b]);
+        blocks = std::max(blocks, plan.blocks_s[b]);
+        keys += ctx[b];
+    }
+    const double head_scores = p->per_head ? keys * s->n_q_heads : 0.;
+    const double rounds = std::max(1., (double)slots / slots_now);
+    const double stream = (8000. + 12500. * ceil(rounds) + 29.5 * rounds * chunk + 0.0032 * head_scores * blocks) *
+                          (blocks > 2 ? 1.08 : 1.12);
+    const int n_cu = device_cus(), calls = (max_q + plan.block_pos - 1) / plan.block_pos;
+    const double rounds2 = (double)calls * ((plan.n_items + n_cu - 1) / n_cu);
+    const double two = 5200. * calls + rounds2 * (17900. + plan.chunk * (4.5 + 6.3 * plan.row_tiles)) +
+                       0.0044 * head_scores * calls;
+    return stream < two;
+}
+
 // The streaming one sweep (verify_stream.hip) with an fp32 stash: chunks of at
 // most what half a CU's LDS holds for each sequence's rows, shortened evenly
 // when the call has fewer chunks than the device's workgroup slots.  Up to 40
-// rows are one row block, taken instead of two sweeps for at most 128 chunks
-// per unit: more chunks keep too many of the slots waiting for one unit (36
-// rows, 228 chunks per 131K-key head: 145 against 140 us), while a ragged
-// batch of 16K-64K keys with up to 40 rows takes 292 us against 383 us.  More
-// rows would make chunks short and their waits long (48 rows over 4 x 64K keys
-// as one block: 330 us against 275 us for two sweeps) and run in blocks of at
-// most 32, by the rule below.  False, too, where the device does not hold two
+// rows are one row block; more would make chunks short and their waits long
+// (48 rows over 4 x 64K keys as one block: 330 us against 275 us for two
+// sweeps) and run in blocks of at most 32.  Taken instead of the
+// one-workgroup-per-chunk one sweep over several rounds (24 rows over 66000 to
+// 86000 keys 0.90-0.95 of its time, 28 and 32 rows 0.92-0.98), and instead of
+// two sweeps where it is expected to be faster, for at most stream_group_max()
+// chunks per exchange group.  False, too, where the device does not hold two
 // workgroups per CU (or cannot be asked).
-bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, VerifyPlan* plan) {
+bool plan_stream(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql, VerifyPlan* plan) {
     constexpr int kTileKeys = 32, kMinTiles = 4, kSpreadTiles = 24, kMaxChunksPerHead = 256;
     constexpr int kOneBlockRows = 40, kBlockRows = 32;
     plan->stream = false;
@@ -253,23 +298,7 @@ bool plan_stream(const ssl_shape* s, const int32_t* ctx, const int32_t* ql, Veri
     // (a captured call takes one of the workspace's epochs per group)
     if ((int64_t)s->batch * s->n_kv_heads * plan->stream_blocks > kEpochWords) return false;
     if (slots > (1 << 30) / kVerifyRowCap) return false;
-    if (plan->stream_blocks > 1) {
-        // Row blocks, where they are the faster of the two: a round of the
-        // streaming kernel takes about 0.045 us * (chunk + 200), one of two
-        // sweeps over 64 rows 0.034 us * (chunk + 512) for each row block.
-        // (8 KV heads; 128 rows: 8000 keys 32 against 66 us, 20K 75 / 100, 40K
-        // 138 / 219, but 4 x 32K 429 / 307; 64 rows: 20K 39 / 49, 65K 137 / 85;
-        // 48 rows: 4 x 9000 53 / 82, 2 x 65K 242 / 160.)
-        int chunk = 0, max_q = 0;
-        for (int b = 0; b < s->batch; ++b) {
-            chunk = std::max(chunk, plan->chunk_s[b]);
-            max_q = std::max(max_q, ql[b]);
-        }
-        const int n_cu = device_cus();
-        const double rounds = std::max(1.0, (double)slots / slots_now);
-        const int64_t rounds2 = ((int64_t)plan->n_items + n_cu - 1) / n_cu * ((max_q + plan->block_pos - 1) / plan->block_pos);
-        if (rounds * (chunk + 200) * 45 >= (double)rounds2 * (plan->chunk + 512) * 34) return false;
-    }
+    if (!one_sweep_wins(*plan, p) && !stream_beats_two_sweeps(s, p, ctx, ql, *plan, slots, slots_now)) return false;
     plan->stream = true;
     plan->stream_slots = (int)slots;
     return true;
@@ -435,7 +464,7 @@ int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, con
             plan->pos_s[b] = ql[b];
         }
     } else if (!one_round) {
-        plan_stream(s, ctx, ql, plan);
+        plan_stream(s, p, ctx, ql, plan);
     }
     if (plan->stream) {
         int64_t rows_out = 0;
@@ -461,17 +490,8 @@ int plan_verify(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, con
     return SSL_OK;
 }
 
-// AUTO takes one sweep where it fits and a KV head has at most 32 verify rows,
-// or more when it runs in one round of workgroups or (up to 48 rows) in the
-// streaming form; over several rounds at 33-64 rows (one wave per SIMD,
-// logits of every row in LDS) the one-workgroup-per-chunk kernel waits
-// across rounds and two sweeps are faster (70B shape: 457 vs 336 us), while
-// in one round it wins (44 rows at 16K: 26.1 vs 36.5 us; 48 rows at 8K: 21.8
-// vs 29.6 us; 64 rows at 8K: 25.2 vs 34.0 us).
 bool use_one_sweep(const VerifyPlan& plan, const ssl_params* p) {
-    if (plan.stream) return true;
-    if (!plan.fused_ok || p->verify_mode == SSL_VERIFY_TWO_SWEEP) return false;
-    return p->verify_mode == SSL_VERIFY_ONE_SWEEP || plan.row_tiles <= 2 || plan.pipe || plan.one_round;
+    return plan.stream || one_sweep_wins(plan, p);
 }
 
 struct DraftPlan {
@@ -682,7 +702,7 @@ int ssl_verify_plan(const ssl_shape* shape, const ssl_params* params, const int3
         *items_out = plan.stream_slots;
         return SSL_OK;
     }
-    *schedule_out = !one ? SSL_VERIFY_TWO_SWEEP : plan.pipe ? SSL_VERIFY_ONE_SWEEP_PERSISTENT : SSL_VERIFY_ONE_SWEEP;
+    *schedule_out = !one ? SSL_VERIFY_TWO_SWEEP : SSL_VERIFY_ONE_SWEEP;
     *chunk_out = one ? plan.fused_chunk : plan.chunk;
     *items_out = one ? plan.fused_slots : plan.n_items;
     return SSL_OK;

@@ -40,12 +40,12 @@ def lib(tmp_path_factory):
     B._lib = saved
 
 
-def plan(lib, hq, hkv, ctx, ql, mode=B.VERIFY_AUTO, cus=0):
+def plan(lib, hq, hkv, ctx, ql, mode=B.VERIFY_AUTO, cus=0, per_head=False):
     """(schedule, chunk, items, workspace bytes) or the status."""
     B._lib = lib
     B.set_cu_budget(cus)
     shape = B.Shape(len(ctx), hq, hkv, 128, max(ctx), max(ql))
-    p = B.make_params(0.088, budget=64, verify_mode=mode)
+    p = B.make_params(0.088, budget=64, verify_mode=mode, per_head=per_head)
     try:
         return B.verify_plan(shape, p, ctx, ql) + (B.verify_workspace_bytes(shape, p, ctx, ql),)
     except B.SSLError as e:
@@ -81,3 +81,14 @@ def test_every_shape_has_a_plan(lib):
             assert chunk >= 32 and items >= len(ctx) * hkv and nbytes > 0
             met.add(sch)
     assert met == {B.VERIFY_ONE_SWEEP, B.VERIFY_TWO_SWEEP, B.VERIFY_ONE_SWEEP_PERSISTENT}
+
+
+# (hq, hkv, contexts, positions, per head, schedule): measured on an MI355X, the form that is faster
+@pytest.mark.parametrize("hq,hkv,ctx,q_len,per_head,schedule", [
+    (64, 8, [20011], 16, False, B.VERIFY_ONE_SWEEP_PERSISTENT), (64, 8, [9246] * 3, 7, True, B.VERIFY_TWO_SWEEP),
+    (32, 8, [42384] * 2, 12, False, B.VERIFY_TWO_SWEEP), (32, 8, [9000] * 4, 12, False, B.VERIFY_ONE_SWEEP_PERSISTENT),
+    (64, 8, [32768] * 4, 16, False, B.VERIFY_TWO_SWEEP), (32, 8, [131072], 9, False, B.VERIFY_TWO_SWEEP),
+    (32, 8, [70000], 7, False, B.VERIFY_ONE_SWEEP_PERSISTENT)])
+def test_streaming_or_two_sweeps(lib, hq, hkv, ctx, q_len, per_head, schedule):
+    r = plan(lib, hq, hkv, ctx, [q_len] * len(ctx), per_head=per_head)
+    assert r[0] == schedule, r
