@@ -320,7 +320,7 @@ int ssl_select_workspace(const ssl_shape *shape, const ssl_params *params,
  * partitions of every unit exchange inside one kernel (calls of at most 256
  * partitions whose units' partitions fit in half of what the device holds at
  * once), 0 otherwise (a workgroup per unit for contexts of at most 65536
- * positions, less for fewer than 19 units, three kernels for longer ones); *part_out = positions per
+ * positions, less for fewer than 30 units, three kernels for longer ones); *part_out = positions per
  * partition, *parts_out = partitions of the longest context.  Host only. */
 int ssl_select_plan(const ssl_shape *shape, const ssl_params *params,
                     const int32_t *ctx_len_host, int32_t *one_kernel_out, int32_t *part_out,

@@ -713,11 +713,12 @@ bool unit_setup() {
 
 // Whether a workgroup per unit is the faster of the two: its time grows with
 // the context only, that of the three kernels with the units' partitions
-// (whole steps, budget 2048, us, three kernels / a workgroup per unit: 12 units
+// (whole steps, us, three kernels / a workgroup per unit: budget 2048, 12 units
 // of 65536 positions 114.0 / 118.1, 16 140.2 / 144.3, 24 193.3 / 193.2, 32
-// 312.5 / 306.0; 12 of 56000 107.3 / 108.9).
+// 312.5 / 306.0, 12 of 56000 107.3 / 108.9; budget 105, 16 of 56973 148 / 157;
+// budget 171, 10 of 52157 101 / 107).
 bool unit_is_faster(int max_t, int n_units) {
-    return max_t <= 2 * kUnitRound && max_t <= 47000 + 1000 * n_units;
+    return max_t <= 2 * kUnitRound && max_t <= 42000 + 800 * n_units;
 }
 
 // A workgroup per unit (contexts of at most 2 * kUnitRound positions).

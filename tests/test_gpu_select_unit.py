@@ -22,9 +22,10 @@ CASES = {
     "run16": ([8193, 16384, 8192 + 36, 40], 8, 4, 32, 1024),
     "run32": ([16385, 32768, 3, 20011], 8, 0, 0, 4096),
     "two-rounds": ([32769, 65536, 32768 + 36, 32768 + 37, 100], 4, 4, 32, 4096),
-    # 19 units, enough for a workgroup per unit up to 65536 positions; 18 take three kernels there
-    "two-rounds-19": ([65536], 19, 4, 32, 4096),
-    "three-kernels-18": ([65536, 32769], 9, 4, 32, 4096),
+    # 30 units, enough for a workgroup per unit up to 65536 positions; 29 (and the 20 above) take
+    # three kernels there
+    "two-rounds-30": ([32769, 65536, 32768 + 36, 32768 + 37, 100], 6, 4, 32, 4096),
+    "three-kernels-29": ([65536], 29, 4, 32, 4096),
 }
 
 
