@@ -1185,7 +1185,9 @@ namespace {
 // the CUs and more than 256 draft entries per CU, which it drafts while its
 // selections are at hand (48 units of 4096 positions, 192 partitions: budget
 // 4096 47.2 us against 49.7, budget 1024 43.8 / 43.6; but 32 units of 3000 with
-// all positions selected, 96 partitions, 33.7 / 30.9).  The
+// all positions selected, 96 partitions, 33.7 / 30.9), and where it exchanges
+// nothing, a single partition of which every position is selected (8 units of
+// 329 positions 23.6 / 25.9).  The
 // other form's workspace must fit the one-kernel form's.
 constexpr int kUnitStepMaxCtx = 16384;
 
@@ -1196,7 +1198,12 @@ bool step_unit_select(const ssl_shape* shape, const ssl_params* params, const in
     DraftPlan dp;
     if (plan_draft(&us, params, n_idx, &dp) != SSL_OK || dp.bytes > bytes) return false;
     int64_t entries = 0;
-    for (int b = 0; b < shape->batch; ++b) entries += (int64_t)n_idx[b] * us.n_kv_heads;
+    bool all = true;   // every position of every sequence is selected
+    for (int b = 0; b < shape->batch; ++b) {
+        entries += (int64_t)n_idx[b] * us.n_kv_heads;
+        all = all && n_idx[b] == ctx[b];
+    }
+    if (all && plan.parts == 1) return false;
     const int64_t slots = (int64_t)shape->batch * us.n_kv_heads * plan.parts, n_cu = device_cus();
     return slots * 2 < n_cu || entries <= 256 * n_cu;
 }

@@ -42,7 +42,8 @@ def test_step_equals_the_separate_calls(batch, hq, hkv, ctx, budget):
 @pytest.mark.parametrize("batch,hq,hkv,ctx,budget,ql,unit", [
     (1, 4, 2, 16384, 512, 2, True), (1, 4, 2, 16385, 512, 2, False),    # the longest context
     (3, 16, 16, 4096, 1365, 1, True), (3, 16, 16, 4096, 1366, 1, False),    # 256 entries per CU
-    (3, 8, 8, 4096, 4096, 1, True)])                                     # and fewer partitions than half the CUs
+    (3, 8, 8, 4096, 4096, 1, True),                                      # and fewer partitions than half the CUs
+    (2, 8, 8, 1000, 300, 1, True), (2, 8, 8, 1000, 1000, 1, False)])     # one partition, all selected
 def test_the_steps_select_on_both_sides_of_its_lines(batch, hq, hkv, ctx, budget, ql, unit):
     """The step gives the bits of verify, select and draft, or of verify and
     select_draft, whichever its rule names."""
@@ -65,7 +66,7 @@ def test_the_steps_select_on_both_sides_of_its_lines(batch, hq, hkv, ctx, budget
     assert B.exchange_status() == 0
     assert torch.equal(idx, idx_u) and torch.equal(idx, idx_x)
     assert torch.equal(dout, dout_u if unit else dout_x)
-    assert not torch.equal(dout_u, dout_x)   # (the two merge their partial results differently)
+    assert ctx == 1000 or not torch.equal(dout_u, dout_x)   # (the two merge their partial results differently)
 
 
 def test_a_step_that_drafts_over_most_rows_verifies_as_verify_attn():
