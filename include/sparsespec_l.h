@@ -51,8 +51,9 @@
  *    synchronizes only in ssl_exchange_status.  Two calls that share a
  *    workspace must be ordered on one stream.
  *  - Process state kept by the library: a 64-bit call-tag sequence (host),
- *    per device the CU count, the one-sweep verify kernel's raised LDS limit
- *    and its occupancy (host, read once), the CU budget of ssl_set_cu_budget
+ *    per device the CU count, the raised LDS limits of the one-sweep verify,
+ *    the streaming verify and the select with a workgroup per unit and the
+ *    first two's occupancy (host, read once), the CU budget of ssl_set_cu_budget
  *    and the settings of ssl_test_exchange_faults (host), and one exchange
  *    status word per device (device memory, see ssl_exchange_status).
  *  - Calls may be captured in a HIP graph and the graph replayed any number
@@ -141,22 +142,30 @@ typedef struct {
 /* How ssl_verify_attn schedules its work (results agree to rounding):
  *  AUTO       a one-sweep schedule where one fits and a KV head has at most
  *             32 verify rows, or more when its chunks run in one round of
- *             workgroups, or up to 48 when the streaming form runs (their
- *             measured sweet spots), else the two-sweep one;
+ *             workgroups, or in the streaming form where that is expected to
+ *             be faster than two sweeps (their measured sweet spots), else the
+ *             two-sweep one;
  *  TWO_SWEEP  a K-only pass for the row statistics, then a K+V pass;
  *  ONE_SWEEP  a single K+V pass whose chunks of one (sequence, KV head)
- *             exchange row statistics while resident together: one
- *             workgroup per chunk when every chunk of the call runs in one
- *             round of workgroups (a (sequence, KV head) may then span at most
- *             128 chunks of at most 2048 / 1024 / 640 / 512 keys for up to
- *             16 / 32 / 48 / 64 verify rows per KV head), else, for up to 48
- *             rows, by a streaming kernel that runs two workgroups per CU over
- *             any number of rounds and keeps its probabilities in 16-bit form
- *             (relative error 2^-11; probabilities below 2^-54 of the row's
- *             running maximum count as 0) when a (sequence, KV head) takes at
- *             most 64 chunks of at most 2048 / 1024 / 640 keys, else in fp32
- *             (at most 40 rows and 128 chunks); SSL_ERR_UNSUPPORTED when none
- *             fits.
+ *             exchange row statistics while resident together.  It needs one
+ *             of two forms to fit, else SSL_ERR_UNSUPPORTED: one workgroup per
+ *             chunk (a (sequence, KV head) may span at most 128 chunks of at
+ *             most 2048 / 1024 / 640 / 512 keys for up to 16 / 32 / 48 / 64
+ *             verify rows per KV head), or, for up to 48 rows, chunks of the
+ *             same lengths, at most 64, by a streaming kernel that runs two
+ *             workgroups per CU over any number of rounds and keeps its
+ *             probabilities in 16-bit form (relative error 2^-11;
+ *             probabilities below 2^-54 of the row's running maximum count as
+ *             0).  The first is taken when all chunks of the call run in one
+ *             round of workgroups, else the second where it fits, else the
+ *             streaming kernel with its probabilities in fp32 where that fits
+ *             (at most 128 chunks per row block: one block up to 40 rows,
+ *             blocks of at most 32 rows above), else the first over several
+ *             rounds.  AUTO takes the fp32 form also where neither fits.
+ * The streaming kernel holds probabilities before their normalization of up
+ * to 2^32 (16-bit form: 2^8), two sweeps of at most 1: elements of v above
+ * about 2^90 in magnitude can overflow its fp32 sums where two sweeps' would
+ * not.
  * ssl_verify_plan reports the streaming form as
  * SSL_VERIFY_ONE_SWEEP_PERSISTENT (an output only, not a request). */
 enum {

@@ -275,7 +275,7 @@ __device__ __forceinline__ void stream_chunk(const StreamArgs& fa, const SChunk&
                             8 * (tid & 15));
     }
     const int ntile = (k.key_end - k.key_begin + kTile - 1) / kTile;
-        const size_t cache_off = (size_t)k.unit * a.max_ctx * kHeadDim;
+    const size_t cache_off = (size_t)k.unit * a.max_ctx * kHeadDim;
     const int pages = kPaged ? wave_pages(a, k.b, k.key_begin, ntile, wave, lane) : 0;
     const int k_off = a_row_key(m16) * (kHeadDim * 2) + 16 * G;
     const int v_off = G * (kHeadDim * 2) + 16 * m16;

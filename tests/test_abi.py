@@ -508,9 +508,9 @@ def test_verify_plan_follows_the_cu_budget(lib, cu_budget):
     one round of workgroups and every chunk of a (sequence, KV head) resident
     at once, within half of what the CUs hold (one workgroup per CU here): the
     32K workload's heads take 32 chunks of 1024 keys (the LDS stash's limit at
-    28 rows).  Below 256 CUs the persistent form takes over (a grid of the
-    budget, at most one grid of chunks per head, 1024 keys of 16-bit stash),
-    and below 32 CUs neither fits: two sweeps."""
+    28 rows).  Below 256 CUs the streaming form takes over (16-bit codes, at
+    most a chunk per CU and head, of at most 1024 keys), and below 32 CUs
+    neither fits: two sweeps."""
     s, p, ctx, ql = _plan_32k()
     cu_budget(256)
     assert B.verify_plan(s, p, ctx, ql) == (B.VERIFY_ONE_SWEEP, 1024, 256)
@@ -530,17 +530,17 @@ def test_verify_plan_follows_the_cu_budget(lib, cu_budget):
     q_a, q_p = _i32(*ql)
     assert lib.ssl_verify_workspace(ctypes.byref(s), ctypes.byref(one), ctx_p, q_p,
                                     ctypes.byref(n)) == B.SSL_ERR_UNSUPPORTED
-    # a short context still takes one sweep in a small budget (persistent: its
-    # 32 chunks over 16 workgroups)
+    # a short context still takes one sweep in a small budget (streaming: its
+    # 32 chunks over 16 CUs)
     s2, p2, ctx2, ql2 = _plan_32k(T=4096)
     assert B.verify_plan(s2, p2, ctx2, ql2)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
 
 
 def test_persistent_plan_limits(lib, cu_budget):
-    """The persistent form: at most 48 rows per KV head (its kernel is built for
-    three row tiles), at most 64 chunks per head, a grid of what the budget
-    holds and never more workgroups than chunks; its chunks a multiple of 128
-    keys within the two 16-bit stash buffers' limit."""
+    """The streaming form over 16-bit codes: at most 48 rows per KV head (its
+    kernel is built for three row tiles), at most 64 chunks per head, a
+    workgroup each; its chunks a multiple of 128 keys within what half a CU's
+    LDS holds of codes."""
     cu_budget(64)
     for rows_q, group, ok in ((7, 4, True), (6, 8, True), (16, 4, False)):
         s, p, ctx, ql = _plan_32k(rows_q=rows_q, group=group)
@@ -558,7 +558,7 @@ def test_persistent_plan_limits(lib, cu_budget):
 def test_auto_one_sweep_at_three_row_tiles_needs_one_round(lib, cu_budget):
     """33-64 rows per KV head: AUTO takes the one-workgroup-per-chunk one sweep
     when its chunks run in one round of workgroups (44 rows at 16K: 256 chunks
-    of 512 keys), the persistent form where that applies, and two sweeps where
+    of 512 keys), the streaming form where that applies, and two sweeps where
     neither does (48 rows over 64K keys per head: 103 chunks of 640 keys)."""
     cu_budget(256)
     s, p, ctx, ql = _plan_32k(rows_q=11, group=4, T=16384)
@@ -566,12 +566,12 @@ def test_auto_one_sweep_at_three_row_tiles_needs_one_round(lib, cu_budget):
     assert B.decode_step_plan(s, p, ctx, ql) is True
     s, p, ctx, ql = _plan_32k(rows_q=6, group=8, T=8192)
     assert B.verify_plan(s, p, ctx, ql)[0] == B.VERIFY_ONE_SWEEP
-    s, p, ctx, ql = _plan_32k(rows_q=9, group=4, T=32768)   # 416 chunks of 640: persistent
+    s, p, ctx, ql = _plan_32k(rows_q=9, group=4, T=32768)   # 416 chunks of 640: streaming
     assert B.verify_plan(s, p, ctx, ql)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
     s, p, ctx, ql = _plan_32k(rows_q=6, group=8, T=65536, batch=4)
     assert B.verify_plan(s, p, ctx, ql)[0] == B.VERIFY_TWO_SWEEP
-    # 64 rows (four row tiles): one sweep in one round, else two sweeps (the
-    # persistent form is built for up to three row tiles)
+    # 64 rows (four row tiles): one sweep in one round, else two sweeps (codes
+    # are built for up to three row tiles, and without a GPU nothing else)
     s, p, ctx, ql = _plan_32k(rows_q=16, group=4, T=4096)
     assert B.verify_plan(s, p, ctx, ql)[0] == B.VERIFY_ONE_SWEEP
     s, p, ctx, ql = _plan_32k(rows_q=8, group=8, T=32768)

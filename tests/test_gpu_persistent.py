@@ -1,14 +1,14 @@
-"""GPU parity of the persistent one-sweep verify schedule.
+"""GPU parity of the streaming one-sweep verify schedule over 16-bit codes
+(VERIFY_ONE_SWEEP_PERSISTENT in the plan).
 
 Where one-sweep chunks would take more than one round of workgroups, verify
-runs a persistent grid that takes every grid-th chunk and keeps two chunks'
+runs two workgroups per CU over any number of rounds and keeps a chunk's
 probabilities in 16-bit form (relative error 2^-11).  These cases lower the
 CU budget (ssl_set_cu_budget) so that small shapes, which the oracle checks
-element by element, take that schedule with several chunks per workgroup,
-units that straddle two rounds, ragged contexts and row counts, and 16, 32
-and 48 rows per KV head; the paged cache and per-head scores take it too, a
-captured graph replays it, and forced exchange faults make it give up
-cleanly."""
+element by element, take that schedule with several chunks per unit and CU,
+ragged contexts and row counts, and 16, 32 and 48 rows per KV head; the paged
+cache and per-head scores take it too, a captured graph replays it, and forced
+exchange faults make it give up cleanly."""
 import numpy as np
 import pytest
 import torch
@@ -36,7 +36,7 @@ def _poison(w):
 
 # name: (workload, CU budget)
 CASES = {
-    # 28 rows (two row tiles), three sequences, units of 3-5 chunks over 16 workgroups
+    # 28 rows (two row tiles), three sequences, units of 3-5 chunks over 16 CUs
     "kv8-rows28": (lambda: _poison(generate(
         501, name="kv8-rows28", batch=3, n_q_heads=32, n_kv_heads=8, ctx_len=[3000, 1700, 4097],
         q_len=[7, 3, 5], max_ctx=4100, max_q=7, budget=300, heavy_hitters=4)), 16),
@@ -49,7 +49,7 @@ CASES = {
         503, name="kv8-rows48-g8", batch=2, n_q_heads=64, n_kv_heads=8, ctx_len=[2600, 1300],
         q_len=[6, 4], max_ctx=2600, max_q=6, budget=200)), 8),
     # sixteen sequences of 1-3000 keys and 1-8 positions: many short units,
-    # several per round, some of a single chunk
+    # several at once, some of a single chunk
     "b16-short": (lambda: _poison(generate(
         505, name="b16-short", batch=16, n_q_heads=8, n_kv_heads=2,
         ctx_len=[2433, 2551, 917, 2110, 2226, 53, 935, 2997, 601, 2338, 1248, 1530, 2013, 235, 658, 983],
@@ -122,7 +122,7 @@ def test_persistent_verify_matches_oracle(name):
 
 def test_persistent_bf16_outputs_and_single_round_agreement():
     """bf16 outputs stay within half a bf16 ulp of the oracle's bar, and the
-    persistent scores agree with the one-workgroup-per-chunk schedule's
+    streaming scores agree with the one-workgroup-per-chunk schedule's
     (fp32 stash) to the 16-bit code's 2^-11."""
     make, budget = CASES["kv8-rows28"]
     w = make()
@@ -165,7 +165,7 @@ def test_persistent_per_head_scores():
 
 
 def test_persistent_paged_matches_dense():
-    """Over a shuffled page pool the persistent schedule gives the dense call's
+    """Over a shuffled page pool the streaming schedule gives the dense call's
     bits."""
     from test_gpu_paged import paged
     make, budget = CASES["kv8-rows28"]
@@ -189,7 +189,7 @@ def test_persistent_paged_matches_dense():
 
 
 def test_persistent_graph_replays():
-    """A captured persistent call, replayed over new cache contents, matches
+    """A captured streaming call, replayed over new cache contents, matches
     the eager call on every replay (the exchange epochs)."""
     make, budget = CASES["kv2-rows16"]
     w = make()
