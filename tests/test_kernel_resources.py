@@ -24,11 +24,11 @@ MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 # kernels that must use no scratch (demangled-name prefixes)
 NO_SCRATCH = (
     "verify_fused_kernel<1,", "verify_fused_kernel<2,", "verify_fused_kernel<3,",
-    "verify_pipe_kernel<1,", "verify_pipe_kernel<2,",
+    "verify_stream_kernel", "verify_add_scores_kernel",
     "verify_stats_kernel", "verify_main_kernel", "verify_combine_kernel",
-    "select_fused_kernel", "select_hist_kernel", "select_mark_kernel", "select_finish_kernel",
-    "draft_kernel<0,", "draft_kernel<1,", "draft_materialize_kernel",
-    "greedy_accept_kernel", "spec_",
+    "select_fused_kernel", "select_unit_kernel", "select_hist_kernel", "select_mark_kernel",
+    "select_finish_kernel", "draft_kernel<0,", "draft_kernel<1,", "draft_materialize_kernel",
+    "logit_stats_kernel", "spec_stats_kernel", "spec_mass_kernel", "spec_sample_kernel",
 )
 MAX_SPILL_BYTES = 128
 
@@ -82,6 +82,8 @@ def test_kernels_use_no_scratch(tmp_path):
     k = _kernels(tmp_path)
     assert len(k) >= 60, f"only {len(k)} kernels found"
     hot = {n: v for n, v in k.items() if n.startswith(NO_SCRATCH)}
+    gone = [p for p in NO_SCRATCH if not any(n.startswith(p) for n in hot)]
+    assert not gone, f"no kernel of this name: {gone}"
     assert len(hot) >= 40, f"only {len(hot)} hot kernels found"
     bad = {n: v for n, v in hot.items() if v}
     assert not bad, f"kernels with scratch memory: {bad}"
