@@ -28,7 +28,7 @@ NO_SCRATCH = (
     "verify_stats_kernel", "verify_main_kernel", "verify_combine_kernel",
     "select_fused_kernel", "select_unit_kernel", "select_hist_kernel", "select_mark_kernel",
     "select_finish_kernel", "draft_kernel<0,", "draft_kernel<1,", "draft_materialize_kernel",
-    "logit_stats_kernel", "spec_stats_kernel", "spec_mass_kernel", "spec_sample_kernel",
+    "spec_stats_kernel", "spec_mass_kernel", "spec_sample_kernel",
 )
 MAX_SPILL_BYTES = 128
 
