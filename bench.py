@@ -89,16 +89,26 @@ def kernel_short(name: str) -> str:
 
 def is_paged(short: str) -> bool:
     """Whether a kernel (short name with template arguments) is the paged-cache
-    instance: the last template flag of the verify kernels, mode 3 of the draft."""
+    instance: a template flag of the verify kernels, mode 3 of the draft."""
     if "<" not in short:
         return False
     args = [x.strip() for x in short.split("<", 1)[1].rstrip(">").split(",")]
     k = short.split("<")[0]
     if k == "verify_fused_kernel":   # <row tiles, stream, paged, whole step>
         return len(args) >= 3 and args[2] == "true"
-    if k in ("verify_stats_kernel", "verify_main_kernel", "verify_pipe_kernel"):
-        return len(args) == 2 and args[1] == "true"
+    if k == "verify_stream_kernel":  # <paged, codes, keep in the L2>
+        return args[0] == "true"
+    if k in ("verify_stats_kernel", "verify_main_kernel"):   # <row tiles, paged(, per head)>
+        return len(args) >= 2 and args[1] == "true"
     return k == "draft_kernel" and args[0] == "3"
+
+
+def select_schedule(one_kernel: bool, max_ctx: int, units: int) -> str:
+    """What select runs: the plan says one kernel or not; select.hip takes a
+    workgroup per unit up to 65536 positions, fewer for few units."""
+    if one_kernel:
+        return "one kernel"
+    return "workgroup per unit" if max_ctx <= min(65536, 42000 + 800 * units) else "three kernels"
 
 
 def is_step_kernel(short: str) -> bool:
@@ -633,10 +643,11 @@ def workload_entry(B, n: int, steps: int, warmup: int, torch, np, cpu: bool):
              "n_kv_heads": w.n_kv_heads, "ctx_len": list(map(int, w.ctx_len)),
              "q_len": list(map(int, w.q_len)), "budget": w.budget,
              "verify_schedule": {B.VERIFY_ONE_SWEEP: "one-sweep", B.VERIFY_TWO_SWEEP: "two-sweep",
-                                 B.VERIFY_ONE_SWEEP_PERSISTENT: "one-sweep persistent"}[schedule],
-             "verify_items": vitems, "select_schedule": "one kernel" if sel_one else "three kernels",
+                                 B.VERIFY_ONE_SWEEP_PERSISTENT: "one-sweep streaming"}[schedule],
+             "verify_items": vitems,
+             "select_schedule": select_schedule(sel_one, int(max(w.ctx_len)), w.batch * w.n_kv_heads),
              "select_partitions_per_unit": sel_parts,
-             "step_call": "one kernel" if sts[0].one_kernel else "verify, then select_draft",
+             "step_call": "one kernel" if sts[0].one_kernel else "verify, then select and draft",
              "step_us": round(step_us, 3), "step_alg_bytes": sum(nbytes.values()),
              "step_hbm_frac": round(sum(nbytes.values()) / (step_us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
              "steps": steps, "kv_copies_rotated": n_copies, "calls": {}}
@@ -742,7 +753,7 @@ def main() -> int:
     vshape = B.Shape(w.batch, w.n_q_heads, w.n_kv_heads, w.head_dim, w.max_ctx, w.max_q)
     schedule, vchunk, vitems = B.verify_plan(vshape, params, w.ctx_len, w.q_len)
     sched_name = {B.VERIFY_ONE_SWEEP: "one-sweep", B.VERIFY_TWO_SWEEP: "two-sweep",
-                  B.VERIFY_ONE_SWEEP_PERSISTENT: "one-sweep persistent"}[schedule]
+                  B.VERIFY_ONE_SWEEP_PERSISTENT: "one-sweep streaming"}[schedule]
     verify_kernels = {B.VERIFY_ONE_SWEEP: "verify_fused_kernel",
                       B.VERIFY_ONE_SWEEP_PERSISTENT: "verify_stream_kernel",
                       B.VERIFY_TWO_SWEEP: "verify_stats_kernel + verify_main_kernel + verify_combine_kernel"}[schedule]
@@ -891,7 +902,7 @@ def main() -> int:
                    "verify_items": vitems,
                    "step_call": "ssl_decode_step (" + ("one kernel: verify, select and the first "
                                 "draft step" if steps[0].one_kernel else
-                                "verify, then select_draft") + ")"},
+                                "verify, then select and draft") + ")"},
         "gpu_step_us_median": round(statistics.median(step_us), 3),
         "step_alg_bytes": step_total,
         "step_hbm_gbps": round(step_total / (ms_per_step * 1e-3) / 1e9, 1),

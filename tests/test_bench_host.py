@@ -39,3 +39,32 @@ def test_algorithmic_bytes_of_the_32k_workload():
     assert n_idx == [2048]
     assert nb["draft"] == 8 * 2048 * (128 * 2 * 2 + 4) + 32 * 128 * 4
     assert nb["select"] == 8 * 32768 * 4 + 8 * 2048 * 4 + 4
+
+
+@pytest.mark.parametrize("short,paged", [
+    ("verify_stream_kernel<true, false, false>", True), ("verify_stream_kernel<false, true, true>", False),
+    ("verify_fused_kernel<2, true, true, false>", True), ("verify_fused_kernel<2, true, false, true>", False),
+    ("verify_main_kernel<2, true, false>", True), ("verify_main_kernel<2, false, true>", False),
+    ("verify_stats_kernel<4, true>", True), ("draft_kernel<3, 1>", True), ("draft_kernel<0, 1>", False),
+    ("verify_combine_kernel", False)])
+def test_paged_instances_are_told_apart(short, paged):
+    assert bench.is_paged(short) is paged
+
+
+def test_kernel_list_names_every_kernel_of_the_library():
+    """Each __global__ function of the sources is in the benchmark's list."""
+    import re
+    csrc = os.path.join(ROOT, "paper_2607_27735_amd", "csrc")
+    text = "".join(open(os.path.join(csrc, f)).read() for f in os.listdir(csrc))
+    names = set(re.findall(r"__global__[^;{]*?\b(\w+_kernel)\(", text))
+    names.discard("take_status_kernel")   # reads the exchange status, no part of a call
+    assert names and names == set(bench.OUR_KERNELS)
+
+
+@pytest.mark.parametrize("n,schedule", [(2, "one kernel"), (3, "workgroup per unit"), (5, "workgroup per unit")])
+def test_select_schedule_names(n, schedule):
+    from paper_2607_27735_amd import binding as B
+    w = make_config(n)
+    one, _, _ = B.select_plan(B.Shape(w.batch, w.n_q_heads, w.n_kv_heads, 128, w.max_ctx, 1),
+                              B.make_params(w.sm_scale, budget=w.budget), w.ctx_len)
+    assert bench.select_schedule(one, int(max(w.ctx_len)), w.batch * w.n_kv_heads) == schedule
