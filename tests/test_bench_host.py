@@ -61,10 +61,8 @@ def test_kernel_list_names_every_kernel_of_the_library():
     assert names and names == set(bench.OUR_KERNELS)
 
 
-@pytest.mark.parametrize("n,schedule", [(2, "one kernel"), (3, "workgroup per unit"), (5, "workgroup per unit")])
-def test_select_schedule_names(n, schedule):
-    from paper_2607_27735_amd import binding as B
-    w = make_config(n)
-    one, _, _ = B.select_plan(B.Shape(w.batch, w.n_q_heads, w.n_kv_heads, 128, w.max_ctx, 1),
-                              B.make_params(w.sm_scale, budget=w.budget), w.ctx_len)
-    assert bench.select_schedule(one, int(max(w.ctx_len)), w.batch * w.n_kv_heads) == schedule
+def test_select_schedule_names():
+    assert bench.select_schedule(True, 32768, 8) == "one kernel"
+    assert bench.select_schedule(False, 65536, 30) == "workgroup per unit"
+    assert bench.select_schedule(False, 65536, 29) == "three kernels"
+    assert bench.select_schedule(False, 65537, 64) == "three kernels"

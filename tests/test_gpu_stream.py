@@ -10,7 +10,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_common import Dev, abs_v, check_outputs, check_score_mass, check_scores, params_of
+from gpu_common import Dev, abs_v, check_outputs, check_score_mass, check_scores, dev_bf16
 from paper_2607_27735_amd import binding as B
 from paper_2607_27735_amd.workloads import bf16_bits_to_f32, f32_to_bf16_bits, generate
 
@@ -139,6 +139,29 @@ def test_stream_matches_oracle(name, per_head):
         check_score_mass(s, w)
     if "ramp" not in name:
         check_scores(s, s_ref, w.ctx_len)
+
+
+@pytest.mark.parametrize("name", ["codes-rows12", "fp32-rows40", "fp32-blocks128"])
+def test_paged_and_bf16_outputs_give_the_dense_bits(name):
+    """Over a shuffled page pool every form gives the dense call's bits, and its
+    bf16 outputs are the fp32 ones, rounded."""
+    from test_gpu_paged import paged
+    make, budget, _ = CASES[name]
+    w = make()
+    d = Dev(w)
+    B.set_cu_budget(budget)
+    p, p16 = (B.make_params(w.sm_scale, window=w.window, budget=w.budget, out_fp32=f) for f in (True, False))
+    assert B.verify_plan(B.verify_shape(d.q, d.k), p, w.ctx_len, w.q_len)[0] == B.VERIFY_ONE_SWEEP_PERSISTENT
+    out, sc = B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p)
+    out16, sc16 = B.verify_attn(d.q, d.k, d.v, w.ctx_len, w.q_len, p16)
+    kp, vp, bt, _ = paged(w, 64, seed=17)
+    kp, vp, bt = dev_bf16(kp), dev_bf16(vp), torch.from_numpy(bt).cuda()
+    out_p, sc_p = B.verify_attn_paged(d.q, kp, vp, bt, w.max_ctx, w.ctx_len, w.q_len, p)
+    out_p16, _ = B.verify_attn_paged(d.q, kp, vp, bt, w.max_ctx, w.ctx_len, w.q_len, p16)
+    torch.cuda.synchronize()
+    assert B.exchange_status() == 0
+    assert torch.equal(out_p, out) and torch.equal(sc_p, sc) and torch.equal(sc16, sc)
+    assert torch.equal(out16, out.to(torch.bfloat16)) and torch.equal(out_p16, out16)
 
 
 def test_row_blocks_under_capture():
