@@ -1260,19 +1260,20 @@ struct DecodePlan {
     size_t hist_off, seg_off, tag_off, part_off, bytes;
 };
 
-// Whether verify leaves K and V in the L2 for the draft, which reads half of
-// the rows again or more, and the call is small enough for it to matter (its
-// chunks of codes run at one workgroup per CU).  K and V cold, us per step, the
-// streaming hint / without it: 40 units of 4096 positions all selected 46.4 /
-// 43.4, of 2000 with 1024 selected 48.9 / 46.1; with 1024 of 4096 41.9 / 42.2;
-// 64 units of 8191 with 4096 selected (two workgroups per CU) 94.5 / 95.1.
+// Whether verify leaves K and V in the L2 for the draft, which reads two fifths
+// of the rows again or more, in a call whose chunks of codes run at one
+// workgroup per CU.  K and V cold, us per step, the streaming hint / without
+// it: 40 units of 4096 positions all selected 46.4 / 43.4, of 2000 with 1024
+// selected 48.9 / 46.1; with 1024 of 4096 41.9 / 42.2.  Over 1300 random steps
+// the mean ratio without it is 1.008 up to three tenths of the rows, 0.996 in
+// the next tenth, 0.979 in the one after that.
 bool draft_rereads(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const VerifyPlan& v) {
     int64_t keys = 0, rows = 0;
     for (int b = 0; b < s->batch; ++b) {
         keys += ctx[b];
         rows += ssl_index_count(ctx[b], p->k_sink, p->k_recent, p->budget);
     }
-    return v.pipe && v.fused_slots <= device_cus() && 2 * rows >= keys;
+    return v.pipe && v.fused_slots <= device_cus() && 5 * rows >= 2 * keys;
 }
 
 int plan_decode(const ssl_shape* s, const ssl_params* p, const int32_t* ctx, const int32_t* ql,
