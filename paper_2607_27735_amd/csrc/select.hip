@@ -473,9 +473,9 @@ __global__ __launch_bounds__(kSelThreads) void select_fused_kernel(SelectArgs a)
 // into two bit masks (above the threshold's bin, in it), the few in it are
 // listed in position order and resolved by two more radix passes, and each
 // thread emits its mask's bits at its place in the order.  What bounds it is
-// the VALU of one CU: 64-lane steps with a ballot, a mask and a branch per 64
-// scores took 540 cycles each, the bit masks take 100 and the histogram about
-// 200.  Contexts above 32768 positions take a second round through the LDS.
+// the VALU of one CU, which the bit masks spare a ballot, a mask and a branch
+// per 64 scores.  Contexts above 32768 positions take a second round through
+// the LDS.
 // Against the three kernels below, in one stream of calls: 128 units of 8191
 // scores 18.8 -> 11.2 us, 32 of 24000 19.3 -> 14.0, 64 of 65536 29.5 -> 24.1,
 // 512 of 32768 79 -> 30 (log-normal scores, sigma 1.2; with more candidates,

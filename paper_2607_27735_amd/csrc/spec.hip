@@ -18,7 +18,7 @@
 // row merges and the decision are a few KB and are redone by every chunk's
 // workgroup rather than given launches of their own, and the loads of a stage
 // go out together (4 sequences of 6 drafted tokens, 128256-token vocabulary,
-// bf16: 34.6 us of kernel time in five launches, 27.7 us in three).
+// bf16: 34.6 us of kernel time in five launches, 25.5 us in three).
 // Everything is fp32.  The chunk masses and the in-chunk scan add in
 // different orders; when rounding leaves the scan short of the target, the
 // chunk's last element with mass is drawn.

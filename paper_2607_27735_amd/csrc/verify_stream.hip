@@ -9,10 +9,8 @@
 // its LDS and 256 registers per lane each): while one waits, merges and writes
 // scores, the other streams.  Measured per verify call, before (a persistent
 // grid, or two sweeps where that did not fit) and after: 16 chat sequences of
-// 1K-8K keys 106 -> 82 us, 12 paged sequences of 3K-30K keys 201 -> 184 us,
-// 8 sequences of 16K-64K keys and up to 40 rows 383 -> 292 us.  With nothing
-// but its loads the kernel takes as long (the arithmetic is hidden); with
-// nothing after its sweep it streams at 6.7-7.0 TB/s.
+// 1K-8K keys 106 -> 82 us, 12 paged sequences of 3K-30K keys 201 -> 183 us,
+// 8 sequences of 16K-64K keys and up to 40 rows 383 -> 292 us.
 //
 // A workgroup:
 //   1. streams its chunk of K and V once, a wave per 32-key tile, online
@@ -44,7 +42,8 @@
 // holds all of a head's, and the blocks' scores are added by a second, small
 // kernel.
 // (128 rows over 8 heads of 20011 keys: 98.6 us as two blocks of 64 rows of two
-// sweeps each, whose 160 items leave CUs idle; 71.7 us as four of 32 rows.)
+// sweeps each, whose 160 items leave CUs idle; 71.2 us as four of 32 rows, which
+// fetch 164 MB for the 82 MB of K and V, so half of the four reads hit the L2.)
 // Publication, tags, epochs and bounded waits are those of verify_fused.hip.
 // The waits end: workgroups are dispatched in index order, the chunks of a
 // group (of both blocks, where two are interleaved) are consecutive and at most
